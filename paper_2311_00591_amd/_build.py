@@ -6,6 +6,7 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 SOURCES = [os.path.join(PKG, "csrc", "coop_window_search.hip"),
+           os.path.join(PKG, "csrc", "coop_window_sub.hip"),
            os.path.join(PKG, "csrc", "coop_first_fit.hip"),
            os.path.join(PKG, "csrc", "coop_replay.hip"),
            os.path.join(PKG, "csrc", "coop_window_search_real.hip")]

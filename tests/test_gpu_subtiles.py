@@ -1,0 +1,88 @@
+"""The window search on batches large enough for its search on subtiles: the
+kernel takes a batch by the blocks it samples, so both answers of that look
+are tested, at the edges of subtiles (512 starts, 64 blocks past them), tiles
+and request groups, with windows left to the second kernel and blocks too
+large for packed keys.  Bit for bit against the oracle, eagerly and replayed
+from a graph."""
+import os
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+EDGES = [1, 7, 8, 9, 511, 512, 513, 575, 576, 577, 1599, 1600, 1601, 4095, 4096, 4097, 4671, 4672,
+         8191, 8192, 8193]
+
+
+def _batch(pinned, cost, seed):
+    """Snapshots at the edges, and one long one per edge that brings the
+    average to more than 8192 blocks; one long one in four has no pinned
+    block, one in four a huge block."""
+    rng = np.random.default_rng(seed)
+    long_ = (1 << 25) // 1200
+    lens = []
+    for i in range(1230):
+        lens += [EDGES[i % len(EDGES)]] if i < 4 * len(EDGES) else []
+        lens.append(long_ + int(rng.integers(0, 700)))
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.uint64)
+    n = int(off[-1])
+    size = (rng.integers(1, 1 << 12, size=n) * 512).astype(np.uint64)
+    u = rng.random(n)
+    kind = np.where(u < pinned, 2, np.where(u < pinned + 0.15, 0, 1)).astype(np.uint8)
+    c = np.exp(rng.random(n) * np.log(1e12)) if cost == "log" else rng.integers(0, 4, n) \
+        if cost == "ties" else rng.integers(0, 10**6, n)
+    c = np.where(kind == 1, c, 0).astype(np.uint64)
+    reqs = []
+    for b, (s, e) in enumerate(zip(off[:-1].astype(int), off[1:].astype(int))):
+        if e - s > 10000 and b % 4 == 0:
+            kind[s:e] = np.minimum(kind[s:e], 1)
+        if e - s > 10000 and b % 4 == 1:
+            size[s + int(rng.integers(0, e - s))] = 1 << 40
+        total = int(size[s:e].sum())
+        mean = total // (e - s)
+        r = [mean * 3, min(total, mean * 500)] if e - s > 10000 else [mean, total, total + 1]
+        if b % 97 == 0:
+            r = [0, 1, mean * 700, mean * 9000] + [int(mean * x) for x in rng.random(126) * 40]
+        reqs.append(r)
+    req = np.array([x for r in reqs for x in r], dtype=np.uint64)
+    roff = np.concatenate([[0], np.cumsum([len(r) for r in reqs])]).astype(np.uint64)
+    return workloads.Pools(size, c, kind, off, req, roff)
+
+
+@pytest.mark.parametrize("pinned, cost", [(0.3, "uniform"), (0.3, "log"), (0.5, "ties"), (0.02, "uniform")])
+def test_large_batches(pinned, cost):
+    import paper_2311_00591_amd as coop
+    a = _batch(pinned, cost, 7)
+    info = coop.plan_info(a.num_blocks, a.num_segments, a.num_requests)
+    assert info["units"] >= 16 * info["workgroups"] and a.num_blocks >= 8192 * a.num_segments
+    print(f"[gpu case] subtiles: pinned {pinned}, {cost} costs, {a.num_blocks} blocks "
+          f"{a.num_requests} requests", flush=True)
+    want = oracle.window_search(*a.arrays(), threads=min(16, len(os.sched_getaffinity(0))))
+    # memory with the least keys in the partial slots and every deferral bit set
+    nbytes = coop.workspace_size(a.num_blocks, a.num_segments, a.num_requests)
+    memory = torch.zeros(nbytes, dtype=torch.uint8, device="cuda")
+    memory[nbytes * 9 // 10:] = 255
+    ws = coop.WindowSearch(*coop.to_device(a, "cuda"), workspace=memory)
+
+    def check(label):
+        torch.cuda.synchronize()
+        got = ws.out.cpu().numpy().view(np.uint64)
+        bad = np.flatnonzero((got != want).any(axis=1))
+        assert len(bad) == 0, f"{label}: {len(bad)} differ, first {int(bad[0])}"
+
+    ws.launch()
+    check("eager")
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        ws.launch()
+    for r in range(2):
+        ws.out.fill_(-1)
+        g.replay()
+        check(f"replay {r}")
+        ws.launch()
+        check(f"eager after replay {r}")
