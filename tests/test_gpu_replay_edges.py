@@ -6,6 +6,7 @@ every outcome equals the CPU oracle's."""
 import numpy as np
 import pytest
 
+import oracle
 import test_gpu_replay as replay
 
 pytestmark = pytest.mark.gpu
@@ -13,10 +14,10 @@ pytestmark = pytest.mark.gpu
 GRAIN = 512
 
 
-def pools(blocks, ops, seed, ties):
+def pools(blocks, ops, seed, ties, cap=None):
     """Random pools of `blocks` blocks each and `ops` operations on them."""
     rng = np.random.default_rng(seed)
-    P, cap = 3, blocks + 2 * ops + 2
+    P, cap = 3, cap or blocks + 2 * ops + 2
     st = {"size": np.zeros((P, cap), np.uint64), "cost": np.zeros((P, cap), np.uint64),
           "kind": np.full((P, cap), 2, np.uint8), "id": np.zeros((P, cap), np.uint32)}
     tr = {k: np.zeros((P, ops), t) for k, t in
@@ -63,3 +64,22 @@ def test_edges_of_rounds_and_batches(blocks, ops, ties, policy):
     state, trace = pools(blocks, ops, 1000 * blocks + ops, ties)
     assert (state["capacity"] * 31) < 150 * 1024  # held in LDS
     replay.assert_same(state, trace, label, policy)
+
+
+@pytest.mark.parametrize("policy", [replay.WINDOW, replay.GREEDY])
+@pytest.mark.parametrize("blocks,ops", [(1, 6), (2, 16), (64, 24), (257, 24), (1030, 24)])
+def test_pools_that_fill_their_slots(blocks, ops, policy):
+    """The fewest slots that the replay can do with: with no room at one end
+    the blocks at the other have to move, and with none at either end the pool
+    fills its slots."""
+    for seed in range(4):
+        for cap in range(blocks, blocks + ops + 2):
+            state, trace = pools(blocks, ops, seed, False, cap)
+            try:
+                oracle.replay(state, trace, threads=8, policy=policy)
+                break
+            except Exception:  # the oracle refuses a replay that runs out of slots
+                continue
+        label = f"full: {blocks} blocks in {cap} slots, {ops} operations, seed {seed}, {policy}"
+        replay._announce(label)
+        replay.assert_same(state, trace, label, policy)
