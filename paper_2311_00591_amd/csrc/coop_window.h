@@ -355,10 +355,11 @@ constexpr uint32_t kSubHalo = 64;  // blocks after them that it stages
 // among 2^24 (4096 requests) took 31 ms there with a walk of 1024 blocks.
 constexpr uint32_t kSubWalk = 8192;
 // The fewest blocks of a snapshot whose windows the search on subtiles can
-// leave to the second kernel (a walk stops before the snapshot end only if
-// more than kSub + kSubHalo + kSubWalk blocks follow the subtile start, which
-// is at most 7 blocks before the snapshot start).
-constexpr uint64_t kSubDeferMin = kSub + kSubHalo + kSubWalk - 6;
+// leave to the second kernel: a walk stops before the snapshot end only if
+// more than kSub + kSubWalk blocks follow the subtile start, which is at most
+// 7 blocks before the snapshot start.  (A subtile next to a block of 2^37
+// bytes is staged without the kSubHalo blocks, so they do not count.)
+constexpr uint64_t kSubDeferMin = kSub + kSubWalk - 6;
 
 // Batches that the search on subtiles may take: 16 tiles and more for every
 // workgroup, so that most tiles meet bounds from earlier ones and the cold

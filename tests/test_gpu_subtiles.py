@@ -86,3 +86,59 @@ def test_large_batches(pinned, cost):
         check(f"replay {r}")
         ws.launch()
         check(f"eager after replay {r}")
+
+
+# Lengths around the shortest snapshot with windows left to the second kernel
+# (512 starts and a walk of 8192 blocks, less 7 before the snapshot start when
+# a subtile ends without its 64 blocks past the starts; 64 more with them),
+# and where the huge block lies that takes those away: among the starts (plain
+# prefixes), or among the blocks past them.
+FAR = [8697, 8698, 8705, 8730, 8761, 8762]
+HUGE_AT = [None, 0, 511, 512, 575]
+
+
+def _far_batch():
+    rng = np.random.default_rng(11)
+    shapes = [(n, at, 7) for n in FAR for at in HUGE_AT] + [(n, at, 0) for n in FAR[3::2] for at in HUGE_AT]
+    lens, far = [], []
+    for n, at, lead in shapes:
+        lens += [840_000 + (lead - sum(lens)) % 8, n]  # the snapshot starts at `lead` mod 8
+        far.append((len(lens) - 1, at))
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.uint64)
+    n = int(off[-1])
+    short = 1 << 20  # short runs between: 30% pinned
+    u = rng.random(short)
+    kind = np.resize(np.where(u < 0.3, 2, np.where(u < 0.45, 0, 1)).astype(np.uint8), n)
+    size = np.resize((rng.integers(1, 1 << 12, short) * 512).astype(np.uint64), n)
+    cost = np.resize(rng.integers(0, 1 << 40, short).astype(np.uint64), n)
+    mean = 1 << 20
+    reqs = [[mean * 3, mean * 10] for _ in lens]
+    for b, at in far:
+        s, e = int(off[b]), int(off[b + 1])
+        kind[s:e] = np.minimum(kind[s:e], 1)
+        if at is not None:
+            size[s + at] = 1 << 40
+        total = int(size[s:e].sum())
+        reqs[b] = [total, total - 1, total - int(size[e - 1]) + 1, mean * 3]
+    cost[kind != 1] = 0
+    req = np.array([x for r in reqs for x in r], dtype=np.uint64)
+    roff = np.concatenate([[0], np.cumsum([len(r) for r in reqs])]).astype(np.uint64)
+    return workloads.Pools(size, cost, kind, off, req, roff)
+
+
+def test_shortest_snapshots_with_windows_past_the_walk():
+    import paper_2311_00591_amd as coop
+    a = _far_batch()
+    print(f"[gpu case] windows past the walk: {a.num_blocks} blocks {a.num_requests} requests", flush=True)
+    want = oracle.window_search(*a.arrays(), threads=min(16, len(os.sched_getaffinity(0))))
+    dev = coop.to_device(a, "cuda")
+    nbytes = coop.workspace_size(a.num_blocks, a.num_segments, a.num_requests)
+    for fill in (0, 255):  # no deferral bit set beforehand, and every one
+        memory = torch.full((nbytes,), fill, dtype=torch.uint8, device="cuda")
+        ws = coop.WindowSearch(*dev, workspace=memory)
+        ws.out.fill_(-7)
+        ws.launch()
+        torch.cuda.synchronize()
+        got = ws.out.cpu().numpy().view(np.uint64)
+        bad = np.flatnonzero((got != want).any(axis=1))
+        assert len(bad) == 0, f"memory of {fill}: {len(bad)} differ, first {int(bad[0])}: {got[bad[0]]}, {want[bad[0]]}"
