@@ -112,10 +112,11 @@ constexpr uint32_t kMaxWpr = 8;                  // wavefronts that may share on
 // go to the second kernel at once.  Only the speed depends on this guess.
 static_assert(2 * (kTile + kHaloCap) >= 8 * kWalkCap, "a skipped walk is one that would almost surely fail");
 // The fewest blocks of a snapshot whose windows can run past a walk: the
-// walk stops before the snapshot end only if more than kTile + kHaloCap +
-// kWalkCap blocks follow the tile start, which is at most 7 blocks before
-// the snapshot start.
-constexpr uint64_t kDeferMin = kTile + kHaloCap + kWalkCap - 6;
+// walk stops before the snapshot end only if more than kTile + kWalkCap
+// blocks follow the tile start, which is at most 7 blocks before the snapshot
+// start.  (A tile beside a block of 2^37 bytes is staged without a halo, so
+// the halo does not count.)
+constexpr uint64_t kDeferMin = kTile + kWalkCap - 6;
 constexpr uint64_t kPartialBudget = 1ull << 23;  // partial keys (32 B each) before chunks grow
 
 // Prefix-sum element: bytes (or packed key), effective cost, pinned count (or

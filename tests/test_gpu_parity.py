@@ -549,3 +549,29 @@ def test_queued_chunks_sized_by_the_largest_snapshot():
     # chunks than there are partial slots
     assert -(-101 // info["queued_chunk_units"]) + 2 > info["partial_slots"], info
     assert_parity(pools, gpu_search(pools), "queued chunks sized on the device")
+
+
+def test_every_snapshot_leaves_a_window_to_the_second_kernel():
+    """More snapshots than the queue takes, each of the shortest length whose
+    windows a walk can fail to reach the end of: a tile beside a block of 2^37
+    bytes is staged without a halo, so that is one tile and one walk, and the
+    list of deferred jobs needs a place for every one of them."""
+    import paper_2311_00591_amd as coop
+    B, n = 16385, TILE + 1024 + 1
+    _announce(f"{B} snapshots of {n} blocks, every one deferred")
+    size = torch.full((B * n,), 512, dtype=torch.int64, device="cuda")
+    size[::n] = 1 << 37
+    cost = torch.arange(B * n, dtype=torch.int64, device="cuda") % 5
+    kind = torch.ones(B * n, dtype=torch.uint8, device="cuda")
+    offsets = torch.arange(B + 1, dtype=torch.int64, device="cuda")
+    req = torch.full((B,), (1 << 37) + 512 * (n - 1), dtype=torch.int64, device="cuda")
+    ws = coop.WindowSearch(size, cost, kind, offsets * n, req, offsets)
+    ws.out.fill_(-7)
+    got = ws().clone()
+    torch.cuda.synchronize()
+    # the request is the whole snapshot, the only window there is
+    want = torch.zeros_like(got)
+    want[:, 1] = n
+    want[:, 2] = cost.view(B, n).sum(1)
+    bad = (got != want).any(1).nonzero()
+    assert len(bad) == 0, f"{len(bad)} differ, first {int(bad[0])}: {got[bad[0]].tolist()}"
