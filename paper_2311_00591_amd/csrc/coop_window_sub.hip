@@ -1197,8 +1197,13 @@ __device__ __forceinline__ void add_record(const Params& P, RecSum& rec, uint32_
         __hip_atomic_fetch_add(&rec.q, ts.tq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         __hip_atomic_fetch_add(&rec.r, ts.tr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         __hip_atomic_fetch_add(&rec.c, ts.tc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        // (a wavefront's LDS operations complete in order: the sums first)
+        // (a wavefront's LDS operations complete in the order they are issued
+        // in, which the fences keep the compiler from changing: the sums, then
+        // the count; the last one's reads and clears after its count, and
+        // before the place is given to a later tile)
+        __atomic_signal_fence(__ATOMIC_ACQ_REL);
         const uint32_t n = __hip_atomic_fetch_add(&rec.n, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __atomic_signal_fence(__ATOMIC_ACQ_REL);
         if (n == kWaves - 1) {
             const uint64_t idx = (s0 >> kTileLog2) + p - 1;
             if (p != 0 && idx < (P.num_blocks >> kTileLog2)) {
@@ -1211,6 +1216,7 @@ __device__ __forceinline__ void add_record(const Params& P, RecSum& rec, uint32_
             rec.r = 0;
             rec.c = 0;
             rec.n = 0;
+            __atomic_signal_fence(__ATOMIC_ACQ_REL);
             __hip_atomic_fetch_add(&done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
     }
@@ -1311,6 +1317,7 @@ __device__ __forceinline__ void search_units(const Params& P, SearchSmem& sm) {
             while (k >= kRecRing && base == 0 &&
                    uniform(__hip_atomic_load(&sm.rec_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) + kRecRing <= k)
                 __builtin_amdgcn_s_sleep(1);
+            __atomic_signal_fence(__ATOMIC_ACQUIRE);  // (no add to the place before that)
             if (base == 0) add_record(P, sm.rec[k % kRecRing], sm.rec_done, ts, job.s0, p, lane);
             if (now.nt == 0) continue;
             g.live = wanted & ~uniform64(__hip_atomic_load(&sm.deferred, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
