@@ -167,13 +167,15 @@ coop_status_t coop_window_search(const uint64_t *size, const uint64_t *cost,
  * arguments, results and status codes as coop_window_search, without the
  * workspace: the cross-workgroup state (partial keys, arrival counters, the
  * chunk queue, the graph tag word, the list of jobs left to the second
- * kernel and its claim word, per-tile records and deferral bits) lives in a static device array of the
- * library, 32 MiB on every GPU the library runs on, held until the process
- * ends.  Its address is looked up on the first call on a device (with the
+ * kernel and its claim word, per-tile records and deferral bits, the word that
+ * says which search kernel takes a large batch and the costs its workgroups
+ * share) lives in a static device array of the library, 35 MiB on every GPU
+ * the library runs on, held until the process ends.  Its address is looked up on the first call on a device (with the
  * stream's device current) and kept; the call then allocates nothing and
  * never synchronises.
  *
- * The array holds coop_window_search_static_capacity() bytes of workspace.
+ * The array holds coop_window_search_static_capacity() bytes of workspace,
+ * 32 MiB less 256 bytes, and spare room for the last two of these.
  * The search is planned with the largest partial-key budget whose workspace
  * fits (fewer partial slots only make the kernel's chunks longer; the
  * results are the same).  A batch that fits no plan -- roughly more than

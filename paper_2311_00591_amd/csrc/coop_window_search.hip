@@ -2007,6 +2007,7 @@ struct Plan {
     size_t off_pick;       // whether it does, one u64
     size_t off_bounds;     // its shared bounds, one u64 per request (0: none)
     size_t bytes;          // total workspace
+    size_t counted;        // of it, what the limit of the static scratch counts
 };
 
 // Two workgroups of kThreads fit one CU (LDS); 256 CUs.  Workgroups past the
@@ -2022,7 +2023,7 @@ constexpr uint64_t kQueueMaxSegments = 16384;  // every workgroup scans the offs
 constexpr uint64_t kMaxBounds = 1ull << 17;  // requests with shared bounds, at most (1 MiB)
 
 bool make_plan(uint64_t num_blocks, uint64_t num_segments, uint64_t num_requests, Plan* pl,
-               uint64_t partial_budget = kPartialBudget, bool bounds = true) {
+               uint64_t partial_budget = kPartialBudget) {
     if (num_segments > (1ull << 32) || num_blocks > (1ull << 60) || num_requests > (1ull << 40))
         return false;
     const uint64_t nv = (num_blocks >> kTileLog2) + num_segments;
@@ -2117,17 +2118,22 @@ bool make_plan(uint64_t num_blocks, uint64_t num_segments, uint64_t num_requests
     pl->subtiles = subtiles_may_pay(pl->units, pl->grid, num_blocks, num_segments);
     const uint64_t big = num_blocks / kDeferMin < num_segments ? num_blocks / kDeferMin : num_segments;
     pl->defer_cap = nchunks + slices * big;
+    // (the limit of the static scratch has always counted this list as if
+    // such a snapshot had a halo more)
+    const uint64_t big_counted = num_blocks / (kDeferMin + kHaloCap) < num_segments
+                                     ? num_blocks / (kDeferMin + kHaloCap) : num_segments;
     pl->num_rec = num_blocks >> kTileLog2;
     pl->off_rec = pl->off_entries + pl->defer_cap * sizeof(uint4);
     pl->off_bits = pl->off_rec + pl->num_rec * 3 * sizeof(uint64_t);
     // (+32: the layout stays inside even if the workspace is only 8-byte aligned)
     pl->bytes = pl->off_bits + (num_requests * pc + 31) / 32 * sizeof(uint32_t) + 32;
+    pl->counted = pl->bytes - slices * (big - big_counted) * sizeof(uint4);
     // Only the search on subtiles of snapshots that span several chunks shares
     // bounds, and only where their array stays small.
     pl->off_pick = (pl->bytes + 7) & ~static_cast<size_t>(7);
     if (pl->subtiles) pl->bytes = pl->off_pick + sizeof(uint64_t);
     pl->off_bounds = 0;
-    if (bounds && pl->subtiles && pc > 1 && num_requests <= kMaxBounds) {
+    if (pl->subtiles && pc > 1 && num_requests <= kMaxBounds) {
         pl->off_bounds = pl->bytes;
         pl->bytes = pl->off_bounds + num_requests * sizeof(uint64_t);
     }
@@ -2315,7 +2321,14 @@ constexpr size_t kScratchBytes = size_t{32} << 20;
 // The first 256 bytes hold the tag word of captured calls (at the same place
 // whatever the plan); the plan's workspace follows.
 constexpr size_t kScratchTagBytes = 256;
-static __device__ __align__(256) uint64_t scratch[kScratchBytes / sizeof(uint64_t)];
+// Room beside what the limit counts, so that the batches taken, and the
+// partial slots they get, depend on neither: the deferred list's entries that
+// the limit leaves out (a list within kScratchBytes is at most 256 parts in
+// 5114 longer, and two entries a slice), the pick word and the shared bounds.
+constexpr size_t kScratchSpare = size_t{3} << 20;
+static_assert(kScratchBytes / (kDeferMin / kHaloCap) + 2 * kMaxSlices * sizeof(uint4) +
+                      (kMaxBounds + 2) * sizeof(uint64_t) <= kScratchSpare, "the spare room suffices");
+static __device__ __align__(256) uint64_t scratch[(kScratchBytes + kScratchSpare) / sizeof(uint64_t)];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
@@ -2347,14 +2360,13 @@ coop_status_t scratch_address(hipStream_t s, void** ptr) {
 }
 
 // The plan for the static scratch: the largest partial-key budget (a power
-// of two) whose workspace fits, without shared bounds when it fits no plan
-// with them; false when none does.
+// of two) whose workspace fits; false when none does.
 bool static_plan(uint64_t num_blocks, uint64_t num_segments, uint64_t num_requests, Plan* pl) {
-    for (const bool bounds : {true, false}) {
-        for (uint64_t budget = kPartialBudget; budget >= 2; budget >>= 1) {
-            if (!make_plan(num_blocks, num_segments, num_requests, pl, budget, bounds)) return false;
-            if (pl->bytes <= kScratchBytes - kScratchTagBytes) return true;
-        }
+    for (uint64_t budget = kPartialBudget; budget >= 2; budget >>= 1) {
+        if (!make_plan(num_blocks, num_segments, num_requests, pl, budget)) return false;
+        if (pl->counted <= kScratchBytes - kScratchTagBytes &&
+            pl->bytes <= kScratchBytes + kScratchSpare - kScratchTagBytes)
+            return true;
     }
     return false;
 }

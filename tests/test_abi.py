@@ -119,6 +119,25 @@ def test_gpu_path_shares_nothing_with_the_oracle():
     assert "import oracle" not in pkg and "from oracle" not in pkg
 
 
+@pytest.mark.parametrize("n, B, most", [
+    (642_000, 1000, 521_872), (54_860_000, 20_000, 512_204), (481_800_000, 100_000, 443_508),
+    (45_227_962, 16, 517_720), (102_063_486, 1, 512_776), (191_281_898, 2, 504_544),
+    (176_501_792, 4000, 504_652)])
+def test_static_entry_takes_the_same_batches(n, B, most):
+    """The most requests that the static scratch takes: what the workspace
+    holds beside the partial keys, tickets, records and the list must not move
+    the limit (the last four: batches that the search on subtiles may take)."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("a batch that fits is launched where there is a GPU")
+
+    def call(Q):
+        return coop.load_library().coop_window_search_static(16, 16, 16, n, 16, B, 16, 16, Q, 16, None)
+
+    assert call(most) == -3  # planned; there is no device to look the scratch up on
+    assert call(most + 1) == -5
+
+
 def test_plan_queue_and_partial_slots():
     # an eighth of the units (a quarter with fewer than 64 snapshots) go
     # through the queue once each workgroup has at least 8; the first chunks
