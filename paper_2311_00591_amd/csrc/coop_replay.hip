@@ -393,7 +393,16 @@ __global__ __launch_bounds__(kThreads) void replay_update_kernel(
 // search's partial results and the barriers dearer.
 constexpr uint32_t kResThreads = 256;
 constexpr uint32_t kResWaves = kResThreads / 64;
-constexpr size_t kStaticResLds = 1024;  // for the kernel's fixed LDS
+constexpr size_t kStaticResLds = 1024;  // the capacity limit leaves this much for fixed LDS
+// Fixed LDS that the kernel uses, at most: two pools of 2632 slots then share
+// a CU (512 such pools of 1024 operations: 1.49 ms under the window policy and
+// 1.72 greedy; 2.61 and 2.96 with 784 bytes, one pool to a CU).
+constexpr size_t kFixedResLds = 304;
+// Wavefronts a SIMD, so pools a CU: five where the pools' LDS allows it (96
+// VGPRs and 4 spilled; 4096 pools of 192 operations: 1.17 ms under the window
+// policy and 1.37 greedy, 1.30 and 1.51 with four), else four without spills
+// (512 pools of 4096 operations: 6.74 and 7.08 ms, 6.76 and 7.10 with five).
+constexpr uint32_t kResSmall = 5, kResLarge = 4;
 
 // LDS bytes for a pool of cap slots, 31 a slot: size (which holds the byte
 // prefix sums during a window search), cost and cost prefix (u64), tensor id
@@ -457,6 +466,13 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
 }
 
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+
+__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, uint32_t lane) {
+    const int src = static_cast<int>(lane);
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(v), src);
+    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(v >> 32), src);
+    return (static_cast<uint64_t>(hi) << 32) | lo;
+}
 
 // A workgroup barrier that orders LDS only: the operations' records on their
 // way in and the outcomes on their way out stay in flight across it.  No
@@ -572,8 +588,7 @@ __device__ void res_replace(const Lds& l, uint32_t n, uint32_t lo, uint32_t hi, 
 // byte prefix sums P overwrite the sizes for the search (P[k] in sz[k],
 // P[n] in sz[n]); the sizes are put back before it returns.  free_bytes
 // receives the pool's free bytes.
-__device__ WinKey res_window(const Lds& l, uint32_t n, uint64_t S, uint64_t* red, WinKey* wred,
-                             uint64_t* free_bytes) {
+__device__ WinKey res_window(const Lds& l, uint32_t n, uint64_t S, WinKey* wred, uint64_t* free_bytes) {
     const uint32_t tid = threadIdx.x, lane = tid & 63u, w = tid >> 6;
     // each thread owns blocks [a, a1): local sums, then a workgroup scan
     const uint32_t per = (n + kResThreads - 1) / kResThreads;
@@ -600,17 +615,14 @@ __device__ WinKey res_window(const Lds& l, uint32_t n, uint64_t S, uint64_t* red
         }
     }
     for (int o = 32; o >= 1; o >>= 1) pf += shfl_xor_u64(pf, o);
-    if (lane == 63) {
-        red[w] = is;
-        wred[w] = WinKey{ic, ir, pf, 0};
-    }
+    if (lane == 63) wred[w] = WinKey{ic, ir, pf, is};
     lds_barrier();
     uint64_t bs = 0, bc = 0, fb = 0;
     uint32_t br = 0;
     for (uint32_t v = 0; v < kResWaves; ++v) {
         fb += wred[v].start;
         if (v < w) {
-            bs += red[v]; bc += wred[v].cost; br += static_cast<uint32_t>(wred[v].bytes);
+            bs += wred[v].end; bc += wred[v].cost; br += static_cast<uint32_t>(wred[v].bytes);
         }
     }
     *free_bytes = fb;
@@ -685,41 +697,46 @@ __device__ WinKey res_window(const Lds& l, uint32_t n, uint64_t S, uint64_t* red
 // Operations are read, and their outcomes written, this many at a time: the
 // records of the next batch are loaded while one is applied, so that no
 // operation waits for global memory (nor, the counter being shared, for the
-// stores of the operation before it).
+// stores of the operation before it).  What every wavefront reads of a record
+// lies in LDS; its cost, and the outcomes, stay in the registers of the lane
+// whose number they have.
 constexpr uint32_t kOpBatch = 8;
 
 struct OpRecord {
-    uint64_t size, cost;
+    uint64_t size;
     uint32_t id;
-    uint8_t op, flags;
+    uint32_t op_flags;  // op | flags << 8
 };
 
+// (indices and counts of a pool in LDS; ~0u is stored as ~0)
 struct Outcome {
-    uint64_t block, w0, w1, cost, free;
+    uint32_t block, w0, w1;
+    uint64_t cost, free;
 };
 
 // Bound by the chain of one pool's operations: each is a scan of the slots, a
 // barrier, and the replacement of a few slots with a move of those behind
 // them (a barrier between its reads and writes, one after).  A window or a
 // chunk is replaced by the tensor and what is left in one move.  512 pools of
-// 4096 operations: 8.77 -> 6.65 ms (window), 8.30 -> 7.12 ms (greedy) with
+// 4096 operations: 8.72 -> 6.74 ms (window), 8.17 -> 7.08 ms (greedy) with
 // records and outcomes in batches, one barrier a scan and one move an
 // allocation; before, every operation waited for its record's loads behind
 // the last one's stores.
-__global__ __launch_bounds__(kResThreads) void replay_resident_kernel(
+template <uint32_t Waves>
+__global__ __launch_bounds__(kResThreads, Waves) void replay_resident_kernel(
     uint64_t* size, uint64_t* cost, uint8_t* kind, uint32_t* id, uint64_t* len, uint64_t cap,
     const uint8_t* op, const uint32_t* op_id, const uint64_t* op_size, const uint64_t* op_cost,
     const uint8_t* op_flags, uint64_t num_ops, int32_t policy, uint64_t* out_block,
     uint64_t* out_window, uint64_t* out_cost, uint64_t* out_free, uint32_t* status) {
     extern __shared__ __align__(16) char lds_raw[];
-    __shared__ uint64_t red[kResWaves];
-    __shared__ WinKey wred[kResWaves];
-    __shared__ Victim vred[kResWaves];
-    __shared__ OpRecord rec[kOpBatch];
-    __shared__ Outcome res[kOpBatch];
+    __shared__ union {
+        WinKey wred[kResWaves];  // window policy
+        Victim vred[kResWaves];  // greedy policy
+        uint64_t red[kResWaves];
+    } part;
     __shared__ uint32_t hit[3];
-    static_assert(sizeof(red) + sizeof(wred) + sizeof(vred) + sizeof(rec) + sizeof(res) +
-                          sizeof(hit) + 64 <= kStaticResLds,
+    __shared__ OpRecord rec[kOpBatch];
+    static_assert(sizeof(part) + sizeof(hit) + sizeof(rec) <= kFixedResLds && kFixedResLds <= kStaticResLds,
                   "the host leaves this much LDS beside the pool");
     const uint32_t tid = threadIdx.x;
     const uint64_t b = blockIdx.x;
@@ -731,33 +748,36 @@ __global__ __launch_bounds__(kResThreads) void replay_resident_kernel(
         res_put(l, k, Block{size[g + k], cost[g + k], id[g + k], kind[g + k]});
     if (tid == 0) hit[0] = ~0u;
     uint32_t turn = 0;
+    OpRecord ahead{};
+    uint64_t ahead_cost = 0, batch_cost = 0;
     const auto load = [&](uint64_t t) {
         const uint64_t o = o0 + t;
-        return OpRecord{op_size[o], op_cost[o], op_id[o], op[o], op_flags[o]};
+        ahead = OpRecord{op_size[o], op_id[o], op[o] | static_cast<uint32_t>(op_flags[o]) << 8};
+        ahead_cost = op_cost[o];
     };
     const auto store = [&](uint64_t t, const Outcome& r) {
         const uint64_t o = o0 + t;
-        out_block[o] = r.block;
-        out_window[2 * o] = r.w0;
-        out_window[2 * o + 1] = r.w1;
+        const auto index = [](uint32_t v) { return v == ~0u ? kNone : static_cast<uint64_t>(v); };
+        out_block[o] = index(r.block);
+        out_window[2 * o] = index(r.w0);
+        out_window[2 * o + 1] = index(r.w1);
         out_cost[o] = r.cost;
         out_free[o] = r.free;
     };
-    OpRecord ahead{};
-    if (tid < kOpBatch && tid < num_ops) ahead = load(tid);
+    Outcome done{};
+    if (tid < kOpBatch && tid < num_ops) load(tid);
     for (uint64_t t0 = 0; t0 < num_ops; t0 += kOpBatch) {
-        if (tid < kOpBatch) {
-            rec[tid] = ahead;
-            if (t0 > 0) store(t0 - kOpBatch + tid, res[tid]);
-            if (t0 + kOpBatch + tid < num_ops) ahead = load(t0 + kOpBatch + tid);
-        }
+        if (tid < kOpBatch) rec[tid] = ahead;
+        batch_cost = ahead_cost;
+        if (tid < kOpBatch && t0 > 0) store(t0 - kOpBatch + tid, done);
+        if (tid < kOpBatch && t0 + kOpBatch + tid < num_ops) load(t0 + kOpBatch + tid);
         lds_barrier();
         const uint32_t count_ops =
             num_ops - t0 < kOpBatch ? static_cast<uint32_t>(num_ops - t0) : kOpBatch;
         for (uint32_t t = 0; t < count_ops; ++t) {
             const OpRecord r = rec[t];
-            const uint32_t kop = uniform(r.op);
-            Outcome out{kNone, kNone, kNone, 0, kNone};
+            const uint32_t kop = uniform(r.op_flags & 0xffu), flags = r.op_flags >> 8;
+            Outcome out{~0u, ~0u, ~0u, 0, kNone};
             if (kop == kOpFree) {
                 const uint32_t j = res_first(n, hit, turn, [&](uint32_t k) {
                     return static_cast<int>(l.id[k] == r.id) & static_cast<int>(l.kd[k] != COOP_FREE);
@@ -789,11 +809,12 @@ __global__ __launch_bounds__(kResThreads) void replay_resident_kernel(
                     uint64_t fb = 0;
                     for (uint32_t j = tid; j < n; j += kResThreads)
                         if (l.kd[j] == COOP_FREE) fb += l.sz[j];
-                    const uint64_t free0 = res_sum(fb, red);
-                    uint64_t count = 0, evc = 0;
+                    const uint64_t free0 = res_sum(fb, part.red);
+                    uint32_t count = 0;
+                    uint64_t evc = 0;
                     while (!evicted) {
                         const uint32_t v = uniform(
-                            greedy_victim(l.sz, l.co, l.kd, l.id, n, r.id, vred));
+                            greedy_victim(l.sz, l.co, l.kd, l.id, n, r.id, part.vred));
                         if (v == ~0u) break;
                         ++count;
                         evc += l.co[v];
@@ -817,15 +838,13 @@ __global__ __launch_bounds__(kResThreads) void replay_resident_kernel(
                     ok = evicted;  // out of evictable tensors: fails, evictions stay
                 } else {
                     uint64_t fb;
-                    const WinKey wk = res_window(l, n, S, red, wred, &fb);
+                    const WinKey wk = res_window(l, n, S, part.wred, &fb);
                     ok = evicted = wk.start != kNone;  // no window: fails, nothing changes
                     if (evicted) {
                         out.free = fb;
-                        out.w0 = wk.start;
-                        out.w1 = wk.end;
+                        out.w0 = lo = uniform(static_cast<uint32_t>(wk.start));
+                        out.w1 = hi = uniform(static_cast<uint32_t>(wk.end));
                         out.cost = wk.cost;
-                        lo = uniform(static_cast<uint32_t>(wk.start));
-                        hi = uniform(static_cast<uint32_t>(wk.end));
                         F = wk.bytes;
                         if (lo > 0 && l.kd[lo - 1] == COOP_FREE) F += l.sz[--lo];
                         if (hi < n && l.kd[hi] == COOP_FREE) F += l.sz[hi++];
@@ -833,8 +852,9 @@ __global__ __launch_bounds__(kResThreads) void replay_resident_kernel(
                         hi = uniform(hi);
                     }
                 }
-                const Block tensor{S, r.cost, r.id,
-                                   (r.flags & kFlagPinned) ? static_cast<uint8_t>(COOP_PINNED)
+                // (the first wavefront's lanes hold the costs, and it alone writes new blocks)
+                const Block tensor{S, readlane_u64(batch_cost, t), r.id,
+                                   (flags & kFlagPinned) ? static_cast<uint8_t>(COOP_PINNED)
                                                            : static_cast<uint8_t>(COOP_EVICTABLE)};
                 if (ok && n - (hi - lo) + 2 > cap) {
                     if (tid == 0) atomicOr(status, kErrCapacity);
@@ -847,7 +867,7 @@ __global__ __launch_bounds__(kResThreads) void replay_resident_kernel(
                 }
                 if (ok) {
                     const Block rest{F - S, 0, 0, COOP_FREE};
-                    const bool split = F != S, left = r.flags & kFlagLeft;
+                    const bool split = F != S, left = flags & kFlagLeft;
                     const uint32_t m = uniform(split ? 2 : 1);
                     const bool first = left || !split;
                     res_replace(l, n, lo, hi, m, first ? tensor : rest, first ? rest : tensor);
@@ -857,13 +877,13 @@ __global__ __launch_bounds__(kResThreads) void replay_resident_kernel(
             } else if (kop == kOpAlloc) {
                 if (tid == 0) atomicOr(status, kErrOperation);
             }
-            if (tid == 0) res[t] = out;
+            if (tid == t) done = out;
         }
         lds_barrier();
     }
     if (num_ops) {
         const uint64_t last = (num_ops - 1) / kOpBatch * kOpBatch;
-        if (tid < kOpBatch && last + tid < num_ops) store(last + tid, res[tid]);
+        if (tid < kOpBatch && last + tid < num_ops) store(last + tid, done);
     }
     // the pool back to its slots; unused slots empty pinned blocks
     for (uint32_t k = tid; k < cap; k += kResThreads) {
@@ -940,12 +960,14 @@ coop_status_t coop_replay(uint64_t* size, uint64_t* cost, uint8_t* kind, uint32_
     if (capacity < 65536 && res_lds + kStaticResLds <= kLdsLimit) {
         hipLaunchKernelGGL(replay_status_kernel, dim3(1), dim3(1), 0, s0, status_out);
         if (hipGetLastError() != hipSuccess) return COOP_ERR_HIP;
+        const auto kernel = res_lds + kFixedResLds <= kLdsLimit / kResSmall
+                                ? replay_resident_kernel<kResSmall> : replay_resident_kernel<kResLarge>;
         if (res_lds > 64 * 1024 &&
-            hipFuncSetAttribute(reinterpret_cast<const void*>(replay_resident_kernel),
+            hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                 hipFuncAttributeMaxDynamicSharedMemorySize,
                                 static_cast<int>(res_lds)) != hipSuccess)
             return COOP_ERR_HIP;
-        hipLaunchKernelGGL(replay_resident_kernel, dim3(static_cast<uint32_t>(num_pools)),
+        hipLaunchKernelGGL(kernel, dim3(static_cast<uint32_t>(num_pools)),
                            dim3(kResThreads), res_lds, s0, size, cost, kind, id, len, capacity, op,
                            op_id, op_size, op_cost, op_flags, num_ops, policy, out_block,
                            out_window, out_cost, out_free, status_out);
