@@ -12,7 +12,9 @@
 //
 // 2. The enqueue functions behind coop_window_search and coop_first_fit,
 //    with the checks as a parameter: the replay's stepwise path calls them on
-//    arrays it builds itself, once per operation, without checks.
+//    arrays it builds itself, once per operation, without checks, and without
+//    the search on subtiles (its pools end in unused slots, most of their
+//    requests ask for nothing, and each look at a batch takes two launches).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -105,7 +107,7 @@ COOP_HIDDEN coop_status_t coop_window_search_enqueue(
     const uint64_t* size, const uint64_t* cost, const uint8_t* kind, uint64_t num_blocks,
     const uint64_t* seg_offsets, uint64_t num_segments, const uint64_t* req_sizes,
     const uint64_t* req_offsets, uint64_t num_requests, coop_window_t* out, void* workspace,
-    size_t workspace_bytes, void* stream, bool check);
+    size_t workspace_bytes, void* stream, bool check, bool subtiles);
 
 COOP_HIDDEN coop_status_t coop_first_fit_enqueue(
     const uint64_t* size, const uint8_t* kind, uint64_t num_blocks, const uint64_t* seg_offsets,

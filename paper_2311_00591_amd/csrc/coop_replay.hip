@@ -999,7 +999,7 @@ coop_status_t coop_replay(uint64_t* size, uint64_t* cost, uint8_t* kind, uint32_
             if (hipGetLastError() != hipSuccess) return COOP_ERR_HIP;
             rc = coop_window_search_enqueue(size, cost, kind, nb, seg, num_pools, req_win,
                                             req_off, num_pools, win, w + l.win_ws,
-                                            l.win_ws_bytes, stream, false);
+                                            l.win_ws_bytes, stream, false, false);
             if (rc != COOP_OK) return rc;
         }
         hipLaunchKernelGGL(replay_update_kernel, dim3(static_cast<uint32_t>(num_pools)),

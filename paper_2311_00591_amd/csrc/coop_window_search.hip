@@ -2206,7 +2206,7 @@ coop_status_t coop_window_search(const uint64_t* size, const uint64_t* cost, con
                                  void* stream) {
     return coop_window_search_enqueue(size, cost, kind, num_blocks, seg_offsets, num_segments,
                                       req_sizes, req_offsets, num_requests, out, workspace,
-                                      workspace_bytes, stream, coop_host::checks_requested());
+                                      workspace_bytes, stream, coop_host::checks_requested(), true);
 }
 
 }  // extern "C"
@@ -2217,12 +2217,14 @@ namespace {
 // and enqueues the search of a batch under plan pl.  The workspace holds
 // the plan's partial keys, arrival counters and queue word; tag_word is
 // the word a captured call's tags come from (inside the workspace, or at a
-// fixed place of the static scratch).
+// fixed place of the static scratch).  subtiles: whether the search on
+// subtiles may take the batch where the plan says so.
 coop_status_t launch_search(const Plan& pl, const uint64_t* size, const uint64_t* cost,
                             const uint8_t* kind, uint64_t num_blocks, const uint64_t* seg_offsets,
                             uint64_t num_segments, const uint64_t* req_sizes,
                             const uint64_t* req_offsets, uint64_t num_requests, coop_window_t* out,
-                            void* workspace, uint64_t* tag_word, hipStream_t s, bool check) {
+                            void* workspace, uint64_t* tag_word, hipStream_t s, bool check,
+                            bool subtiles) {
     if (check) {
         const coop_host::Batch b{size, cost, kind, num_blocks, seg_offsets, num_segments,
                                  req_offsets, num_requests, true};
@@ -2260,9 +2262,10 @@ coop_status_t launch_search(const Plan& pl, const uint64_t* size, const uint64_t
     P.inv_slope = static_cast<double>(num_segments) /
                   (static_cast<double>(num_blocks) / kTile + static_cast<double>(num_segments));
     P.defer_cap = static_cast<uint32_t>(pl.defer_cap);
-    P.pick = pl.subtiles ? reinterpret_cast<uint64_t*>(static_cast<char*>(workspace) + pl.off_pick) : nullptr;
+    subtiles = subtiles && pl.subtiles;
+    P.pick = subtiles ? reinterpret_cast<uint64_t*>(static_cast<char*>(workspace) + pl.off_pick) : nullptr;
     P.subtiles = 0;
-    P.bounds = pl.off_bounds ? reinterpret_cast<uint64_t*>(static_cast<char*>(workspace) + pl.off_bounds) : nullptr;
+    P.bounds = subtiles && pl.off_bounds ? reinterpret_cast<uint64_t*>(static_cast<char*>(workspace) + pl.off_bounds) : nullptr;
 
     // A captured launch replays with the arguments it was recorded with, so
     // its tag cannot come from the host: it comes from the tag word,
@@ -2283,7 +2286,7 @@ coop_status_t launch_search(const Plan& pl, const uint64_t* size, const uint64_t
     }
 
     // Of the two search kernels the one that does not take the batch ends at once.
-    if (pl.subtiles && !launch_subtiles(P, s)) return COOP_ERR_HIP;
+    if (subtiles && !launch_subtiles(P, s)) return COOP_ERR_HIP;
     hipLaunchKernelGGL(coop_window_search_kernel, dim3(static_cast<uint32_t>(pl.grid)),
                        dim3(kThreads), 0, s, P);
     if (hipGetLastError() != hipSuccess) return COOP_ERR_HIP;
@@ -2291,7 +2294,7 @@ coop_status_t launch_search(const Plan& pl, const uint64_t* size, const uint64_t
                                                            : kLongGridWGs;
     // (a form without the search inside the regions for other batches: with it
     // one run of 2^24 blocks took 4249 us instead of 4212)
-    if (pl.subtiles)
+    if (subtiles)
         hipLaunchKernelGGL(coop_window_long_kernel<true>, dim3(static_cast<uint32_t>(long_grid)),
                            dim3(kThreads), 0, s, P);
     else
@@ -2397,7 +2400,7 @@ coop_status_t coop_window_search_static(const uint64_t* size, const uint64_t* co
     uint64_t* tag_word = static_cast<uint64_t*>(base);
     void* workspace = static_cast<char*>(base) + kScratchTagBytes;
     return launch_search(pl, size, cost, kind, num_blocks, seg_offsets, num_segments, req_sizes,
-                         req_offsets, num_requests, out, workspace, tag_word, s, false);
+                         req_offsets, num_requests, out, workspace, tag_word, s, false, true);
 }
 
 }  // extern "C"
@@ -2408,7 +2411,7 @@ coop_status_t coop_window_search_enqueue(const uint64_t* size, const uint64_t* c
                                          const uint64_t* req_sizes, const uint64_t* req_offsets,
                                          uint64_t num_requests, coop_window_t* out,
                                          void* workspace, size_t workspace_bytes, void* stream,
-                                         bool check) {
+                                         bool check, bool subtiles) {
     if (num_requests == 0) return COOP_OK;
     const coop_status_t rc = check_args(size, cost, kind, num_blocks, seg_offsets, num_segments,
                                         req_sizes, req_offsets, out);
@@ -2420,5 +2423,5 @@ coop_status_t coop_window_search_enqueue(const uint64_t* size, const uint64_t* c
                          pl.slices * num_segments + 1;
     return launch_search(pl, size, cost, kind, num_blocks, seg_offsets, num_segments, req_sizes,
                          req_offsets, num_requests, out, workspace, tag_word,
-                         static_cast<hipStream_t>(stream), check);
+                         static_cast<hipStream_t>(stream), check, subtiles);
 }

@@ -19,6 +19,13 @@ EDGES = [1, 7, 8, 9, 511, 512, 513, 575, 576, 577, 1599, 1600, 1601, 4095, 4096,
          8191, 8192, 8193]
 
 
+def _pick_at(coop, n, B, Q):
+    """Where a search's workspace holds the word that says which kernel took
+    the batch (1: subtiles): its last word but for the shared bounds."""
+    shared = Q <= 1 << 17 and coop.plan_info(n, B, Q)["partial_slots"] > 1
+    return coop.workspace_size(n, B, Q) - 8 * (Q if shared else 0) - 8
+
+
 def _batch(pinned, cost, seed):
     """Snapshots at the edges, and one long one per edge that brings the
     average to more than 8192 blocks; one long one in four has no pinned
@@ -142,3 +149,36 @@ def test_shortest_snapshots_with_windows_past_the_walk():
         got = ws.out.cpu().numpy().view(np.uint64)
         bad = np.flatnonzero((got != want).any(axis=1))
         assert len(bad) == 0, f"memory of {fill}: {len(bad)} differ, first {int(bad[0])}: {got[bad[0]]}, {want[bad[0]]}"
+
+
+def test_the_stepwise_replay_stays_on_tiles():
+    """Pools too large for LDS, enough of them for the search on subtiles: an
+    operation's search makes no look at the batch (the word keeps what the
+    memory held before)."""
+    import paper_2311_00591_amd as coop
+    P, cap = 4096, 8192
+    print(f"[gpu case] stepwise replay: {P} pools of {cap} slots", flush=True)
+    n = P * cap
+    assert coop.plan_info(n, P, P)["units"] >= 16 * 512
+    st = {k: torch.zeros(n, dtype=t, device="cuda") for k, t in
+          (("size", torch.int64), ("cost", torch.int64), ("id", torch.int32))}
+    st["kind"] = torch.full((n,), 2, dtype=torch.uint8, device="cuda")
+    for k, v in (("size", 8192), ("kind", 0)):
+        st[k].view(P, cap)[:, 1] = v
+    st["size"].view(P, cap)[:, 0], st["id"].view(P, cap)[:, 0] = 512, 1
+    st["len"], st["capacity"] = torch.full((P,), 2, dtype=torch.int64, device="cuda"), cap
+    row = lambda t, *v: torch.tensor([*v] * P, dtype=t, device="cuda")
+    # an allocation that fits, one that finds no window, one that evicts the first
+    tr = {"op": row(torch.uint8, 0, 0, 0), "op_id": row(torch.int32, 2, 3, 4),
+          "op_size": row(torch.int64, 512, 1 << 40, 8192), "op_cost": row(torch.int64, 7, 7, 7),
+          "op_flags": row(torch.uint8, 1, 1, 1)}
+    need = coop.replay_workspace_size(P, cap)
+    ws = torch.full((need,), 0xab, dtype=torch.uint8, device="cuda")
+    rep = coop.Replay(st, tr, workspace=ws)
+    rep.launch()
+    torch.cuda.synchronize()
+    assert (rep.block.view(P, 3) == torch.tensor([1, -1, 1], device="cuda")).all()
+    assert (rep.window.view(P, 3, 2)[:, 2] == torch.tensor([1, 3], device="cuda")).all()
+    search = need - (coop.workspace_size(n, P, P) + 255) // 256 * 256
+    at = search + _pick_at(coop, n, P, P)
+    assert ws[at:at + 8].tolist() == [0xab] * 8
