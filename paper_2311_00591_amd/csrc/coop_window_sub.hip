@@ -1397,58 +1397,117 @@ __global__ __launch_bounds__(kThreads, 4) void coop_window_sub_kernel(Params P) 
     search_units(P, sm);
 }
 
-// Whether they do, from 512 blocks spread evenly over the batch: by one
-// wavefront, every lane active (there are far more blocks than 512).
-// - An eighth of the blocks or more are pinned: runs are short, few windows
-//   leave a subtile, and its least bytes and costs tell starts apart.  Pools
-//   of 30% pinned blocks, 4 requests each: 705 us on tiles, 487 on subtiles;
-//   64 requests: 3899 and 1554.
-// - 64 requests a snapshot or more share the staging, and either the runs are
-//   still short (a 24th pinned: 5%, 64 requests, 7751 and 5576 us) or most
-//   costs are far below the average, so that the few large ones rule most
-//   windows out (1% pinned, costs over twelve decades, 4096 requests: 98.4 and
-//   67.0 ms).
+// Whether this kernel pays, from kLook stretches of blocks, one a thread of a
+// workgroup: of 64 blocks each, 1024 where many requests share a snapshot (the
+// search then takes milliseconds).  The stretches lie at multiples of the
+// golden ratio of the batch, so that no period of the snapshots' lengths can
+// put them all at the same place of a pool (evenly spaced over 512 pools of
+// 65536 blocks, they met nothing but the pinned block at each pool's start:
+// 354 us on tiles, 685 on subtiles).  It pays when:
+// - No more than three fifths of the open blocks are free or cost nothing:
+//   among windows of cost 0 nothing is passed over, and each is searched for
+//   (clustered pools, 4 requests: 709 us on tiles and 645 on subtiles with 0.57
+//   of them at no cost, 710 and 813 with 0.74; 64 requests: 61 and 52 ms, 61
+//   and 84).
+// - Few requests a snapshot: two of the 512 stretches at most hold no pinned
+//   block.  Runs are then short throughout, few windows leave a subtile, and
+//   its least bytes and costs tell starts apart.  Pools of 30% pinned blocks, 4
+//   requests each: 708 us on tiles, 490 on subtiles; 8% or 10% scattered over
+//   1024 pools of 65536, 4 requests: 661 and 480, 467; 16 requests: 1746 and
+//   840, 760.  The few open stretches are for batches that hold long runs too:
+//   one pool in 64 without a pinned block, requests of 100 to 9000 blocks
+//   there: 1112 and 1220 us; every other pool: 961 and 1350; a sixth of each
+//   pool pinned, at its two ends: 1479 and 1935.  (Scattered pinned blocks
+//   alone would do with fewer: 5%, 4 requests: 664 and 554.  One such pool in
+//   4096 is not seen: 1064 and 1157.)
+// - 64 requests a snapshot or more share the staging, one of the longer
+//   stretches at most is open (one run of 100,000 blocks among 2^24, a request
+//   of 20,000: 128 ms on tiles, 165 on subtiles), and either an eighth of the
+//   short ones at most are (costs of one magnitude, 64 requests, 2, 3 and 4%
+//   pinned: 17.4 ms on tiles, 19.2, 14.1 and 11.3 on subtiles), or five eighths
+//   at most are and most costs are far below the average, so that the few
+//   large ones rule most windows out (costs over twelve decades, 4096
+//   requests, 1% pinned: 98.3 and 67.0 ms; 0.5%: 106 and 105; 0.2%: 134 and
+//   164).
 // Otherwise the windows that leave a subtile cost more than the starts passed
 // over save: 1% pinned, costs of one magnitude, 8 requests: 514 and 1022 us;
 // 4096 requests: 26.0 and 35.2 ms; 3%, 4 requests: 576 and 618 us.
-__device__ bool subtiles_pay(const Params& P, uint32_t lane) {
-    const uint64_t step = P.num_blocks >> 9;
+constexpr uint32_t kLook = kThreads;
+constexpr uint32_t kLookShort = 64, kLookLong = 1024;
+static_assert(kSubBlocks > kLookLong + 15, "the smallest batch holds a stretch at any alignment");
+
+// A wavefront's counts over its stretches.
+struct Look {
+    uint32_t closed_short, closed_long;   // stretches with a pinned block
+    uint32_t open, costless, evictable;   // of the stretches' first blocks
+    uint32_t below;
+    float sum;                            // the evictable ones' costs
+};
+
+__device__ __forceinline__ uint32_t lanes_where(bool is) {
+    return static_cast<uint32_t>(__builtin_popcountll(__ballot(is)));
+}
+
+// (the first workgroup, every thread; every thread gets the answer, the same
+// from call to call: the sums are added in the same order)
+__device__ bool subtiles_pay(const Params& P, Look* looks, uint32_t tid) {
     const bool many = P.num_requests / 64 >= P.num_segments;
-    uint32_t kd[8];
-    uint64_t ct[8];
+    const uint32_t span = many ? kLookLong : kLookShort;
+    // from the first 16-byte boundary at or after the place
+    const uint64_t at = __umul64hi((tid + 1) * 0x9e3779b97f4a7c15ull, P.num_blocks - span - 15);
+    const uint64_t first = at + ((0 - (reinterpret_cast<uintptr_t>(P.kind) + at)) & 15u);
+    const ulonglong2* const kinds = reinterpret_cast<const ulonglong2*>(P.kind + first);
+    const uint32_t kind = P.kind[first];
+    const uint64_t cost = P.cost[first];
+    uint64_t any = 0;
+    auto look = [&](uint32_t j) {
 #pragma unroll
-    for (uint32_t j = 0; j < 8; ++j) {
-        const uint64_t i = (j * 64 + lane) * step;
-        kd[j] = P.kind[i];
-        ct[j] = many ? P.cost[i] : 0;
+        for (uint32_t k = 0; k < kLookShort / 16; ++k) any |= kinds[j + k].x | kinds[j + k].y;
+    };
+    look(0);
+    constexpr uint64_t kPinnedBits = 0xfefefefefefefefeull;  // set in pinned kinds (2 and more) only
+    const bool closed_short = (any & kPinnedBits) != 0;
+    for (uint32_t j = kLookShort / 16; j < span / 16; j += kLookShort / 16) look(j);
+    const bool evictable = kind == COOP_EVICTABLE;
+    float sum = evictable ? static_cast<float>(cost) : 0.0f;
+    if (many)
+        for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    const Look mine{lanes_where(closed_short), lanes_where((any & kPinnedBits) != 0),
+                    lanes_where(kind < COOP_PINNED),
+                    lanes_where(kind < COOP_PINNED && !(evictable && cost != 0)), lanes_where(evictable), 0, sum};
+    if ((tid & 63u) == 0) looks[tid >> 6] = mine;
+    __syncthreads();
+    Look all{};
+    for (uint32_t w = 0; w < kWaves; ++w) {
+        all.closed_short += looks[w].closed_short;
+        all.closed_long += looks[w].closed_long;
+        all.open += looks[w].open;
+        all.costless += looks[w].costless;
+        all.evictable += looks[w].evictable;
+        all.sum += looks[w].sum;
     }
-    uint32_t pinned = 0, evictable = 0, below = 0;
-    float sum = 0;
-#pragma unroll
-    for (uint32_t j = 0; j < 8; ++j) {
-        pinned += static_cast<uint32_t>(__builtin_popcountll(__ballot(kd[j] >= COOP_PINNED)));
-        evictable += static_cast<uint32_t>(__builtin_popcountll(__ballot(kd[j] == COOP_EVICTABLE)));
-        sum += kd[j] == COOP_EVICTABLE ? static_cast<float>(ct[j]) : 0.0f;
-    }
-    if (pinned >= 512 / 8) return true;
-    if (!many) return false;
-    if (pinned >= 512 / 24) return true;
-    for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, 64);
-#pragma unroll
-    for (uint32_t j = 0; j < 8; ++j)
-        below += static_cast<uint32_t>(__builtin_popcountll(__ballot(
-            kd[j] == COOP_EVICTABLE && static_cast<float>(ct[j]) * (8.0f * static_cast<float>(evictable)) < sum)));
-    return 2 * below >= evictable && evictable != 0;
+    if (5 * all.costless > 3 * all.open) return false;
+    if (!many) return all.closed_short >= kLook - kLook / 256;
+    if (all.closed_long < kLook - 1) return false;
+    if (all.closed_short >= kLook - kLook / 8) return true;
+    if (all.closed_short < kLook - kLook * 5 / 8 || all.evictable == 0) return false;
+    const uint32_t below =
+        lanes_where(evictable && static_cast<float>(cost) * (8.0f * static_cast<float>(all.evictable)) < all.sum);
+    if ((tid & 63u) == 0) looks[tid >> 6].below = below;
+    __syncthreads();
+    for (uint32_t w = 0; w < kWaves; ++w) all.below += looks[w].below;
+    return 2 * all.below >= all.evictable;
 }
 
 // Ahead of the searches on the stream: picks the kernel, and clears the shared
 // bounds.
-__global__ __launch_bounds__(256) void coop_window_pick_kernel(Params P) {
-    const uint64_t i = blockIdx.x * 256ull + threadIdx.x;
+__global__ __launch_bounds__(kThreads) void coop_window_pick_kernel(Params P) {
+    __shared__ Look looks[kWaves];
+    const uint64_t i = blockIdx.x * static_cast<uint64_t>(kThreads) + threadIdx.x;
     if (P.bounds && i < P.num_requests) P.bounds[i] = kNone;
-    if (i < 64) {
-        const bool pay = subtiles_pay(P, threadIdx.x);
-        if (i == 0) *P.pick = pay;
+    if (blockIdx.x == 0) {
+        const bool pay = subtiles_pay(P, looks, threadIdx.x);
+        if (threadIdx.x == 0) *P.pick = pay;
     }
 }
 
@@ -1456,7 +1515,8 @@ __global__ __launch_bounds__(256) void coop_window_pick_kernel(Params P) {
 
 bool coop_win::launch_subtiles(const Params& P, hipStream_t s) {
     const uint64_t n = P.bounds ? P.num_requests : 1;
-    hipLaunchKernelGGL(coop_window_pick_kernel, dim3(static_cast<uint32_t>((n + 255) / 256)), dim3(256), 0, s, P);
+    hipLaunchKernelGGL(coop_window_pick_kernel, dim3(static_cast<uint32_t>((n + kThreads - 1) / kThreads)),
+                       dim3(kThreads), 0, s, P);
     if (hipGetLastError() != hipSuccess) return false;
     hipLaunchKernelGGL(coop_window_sub_kernel, dim3(P.grid), dim3(kThreads), 0, s, P);
     return hipGetLastError() == hipSuccess;

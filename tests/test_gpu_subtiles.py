@@ -1,9 +1,9 @@
 """The window search on batches large enough for its search on subtiles: the
 kernel takes a batch by the blocks it samples, so both answers of that look
-are tested, at the edges of subtiles (512 starts, 64 blocks past them), tiles
-and request groups, with windows left to the second kernel and blocks too
-large for packed keys.  Bit for bit against the oracle, eagerly and replayed
-from a graph."""
+are tested (and which one it gave, from its word in the workspace), at the
+edges of subtiles (512 starts, 64 blocks past them), tiles and request groups,
+with windows left to the second kernel and blocks too large for packed keys.
+Bit for bit against the oracle, eagerly and replayed from a graph."""
 import os
 
 import numpy as np
@@ -26,10 +26,10 @@ def _pick_at(coop, n, B, Q):
     return coop.workspace_size(n, B, Q) - 8 * (Q if shared else 0) - 8
 
 
-def _batch(pinned, cost, seed):
+def _batch(pinned, cost, seed, every=4):
     """Snapshots at the edges, and one long one per edge that brings the
-    average to more than 8192 blocks; one long one in four has no pinned
-    block, one in four a huge block."""
+    average to more than 8192 blocks; one long one in `every` has no pinned
+    block (one in two of those a huge block), one in four a huge block."""
     rng = np.random.default_rng(seed)
     long_ = (1 << 25) // 1200
     lens = []
@@ -46,14 +46,16 @@ def _batch(pinned, cost, seed):
     c = np.where(kind == 1, c, 0).astype(np.uint64)
     reqs = []
     for b, (s, e) in enumerate(zip(off[:-1].astype(int), off[1:].astype(int))):
-        if e - s > 10000 and b % 4 == 0:
+        if e - s > 10000 and b % every == 0:
             kind[s:e] = np.minimum(kind[s:e], 1)
+            if every > 4 and b % (2 * every) == 0:
+                size[s + int(rng.integers(0, e - s))] = 1 << 40
         if e - s > 10000 and b % 4 == 1:
             size[s + int(rng.integers(0, e - s))] = 1 << 40
         total = int(size[s:e].sum())
         mean = total // (e - s)
         r = [mean * 3, min(total, mean * 500)] if e - s > 10000 else [mean, total, total + 1]
-        if b % 97 == 0:
+        if b % 97 == 0 or b % every == 0 and every > 4 and e - s > 10000:
             r = [0, 1, mean * 700, mean * 9000] + [int(mean * x) for x in rng.random(126) * 40]
         reqs.append(r)
     req = np.array([x for r in reqs for x in r], dtype=np.uint64)
@@ -61,13 +63,15 @@ def _batch(pinned, cost, seed):
     return workloads.Pools(size, c, kind, off, req, roff)
 
 
-@pytest.mark.parametrize("pinned, cost", [(0.3, "uniform"), (0.3, "log"), (0.5, "ties"), (0.02, "uniform")])
-def test_large_batches(pinned, cost):
+@pytest.mark.parametrize("pinned, cost, every, subtiles", [
+    (0.3, "uniform", 4, 0), (0.3, "log", 4, 0), (0.5, "ties", 4, 0), (0.02, "uniform", 4, 0),
+    (0.3, "uniform", 300, 1), (0.3, "log", 300, 1), (0.5, "ties", 300, 1), (0.15, "uniform", 300, 1)])
+def test_large_batches(pinned, cost, every, subtiles):
     import paper_2311_00591_amd as coop
-    a = _batch(pinned, cost, 7)
+    a = _batch(pinned, cost, 7, every)
     info = coop.plan_info(a.num_blocks, a.num_segments, a.num_requests)
     assert info["units"] >= 16 * info["workgroups"] and a.num_blocks >= 8192 * a.num_segments
-    print(f"[gpu case] subtiles: pinned {pinned}, {cost} costs, {a.num_blocks} blocks "
+    print(f"[gpu case] subtiles {subtiles}: pinned {pinned}, {cost} costs, {a.num_blocks} blocks "
           f"{a.num_requests} requests", flush=True)
     want = oracle.window_search(*a.arrays(), threads=min(16, len(os.sched_getaffinity(0))))
     # memory with the least keys in the partial slots and every deferral bit set
@@ -75,9 +79,11 @@ def test_large_batches(pinned, cost):
     memory = torch.zeros(nbytes, dtype=torch.uint8, device="cuda")
     memory[nbytes * 9 // 10:] = 255
     ws = coop.WindowSearch(*coop.to_device(a, "cuda"), workspace=memory)
+    at = _pick_at(coop, a.num_blocks, a.num_segments, a.num_requests)
 
     def check(label):
         torch.cuda.synchronize()
+        assert memory[at:at + 8].tolist() == [subtiles] + [0] * 7, f"{label}: the other kernel"
         got = ws.out.cpu().numpy().view(np.uint64)
         bad = np.flatnonzero((got != want).any(axis=1))
         assert len(bad) == 0, f"{label}: {len(bad)} differ, first {int(bad[0])}"
@@ -99,17 +105,17 @@ def test_large_batches(pinned, cost):
 # (512 starts and a walk of 8192 blocks, less 7 before the snapshot start when
 # a subtile ends without its 64 blocks past the starts; 64 more with them),
 # and where the huge block lies that takes those away: among the starts (plain
-# prefixes), or among the blocks past them.
-FAR = [8697, 8698, 8705, 8730, 8761, 8762]
-HUGE_AT = [None, 0, 511, 512, 575]
+# prefixes), or among the blocks past them.  (Blocks, place of the huge block,
+# snapshot start mod 8; few enough that the batch still counts as short runs.)
+FAR = [(8697, 0, 7), (8698, None, 7), (8698, 0, 7), (8698, 511, 7), (8698, 512, 7), (8698, 575, 7),
+       (8705, 0, 0), (8705, 575, 0), (8730, 511, 0), (8761, 512, 7), (8762, None, 7), (8762, 575, 7)]
 
 
 def _far_batch():
     rng = np.random.default_rng(11)
-    shapes = [(n, at, 7) for n in FAR for at in HUGE_AT] + [(n, at, 0) for n in FAR[3::2] for at in HUGE_AT]
     lens, far = [], []
-    for n, at, lead in shapes:
-        lens += [840_000 + (lead - sum(lens)) % 8, n]  # the snapshot starts at `lead` mod 8
+    for n, at, lead in FAR:
+        lens += [4_000_000 + (lead - sum(lens)) % 8, n]
         far.append((len(lens) - 1, at))
     off = np.concatenate([[0], np.cumsum(lens)]).astype(np.uint64)
     n = int(off[-1])
@@ -148,6 +154,8 @@ def test_shortest_snapshots_with_windows_past_the_walk():
         torch.cuda.synchronize()
         got = ws.out.cpu().numpy().view(np.uint64)
         bad = np.flatnonzero((got != want).any(axis=1))
+        at = _pick_at(coop, a.num_blocks, a.num_segments, a.num_requests)
+        assert memory[at].item() == 1
         assert len(bad) == 0, f"memory of {fill}: {len(bad)} differ, first {int(bad[0])}: {got[bad[0]]}, {want[bad[0]]}"
 
 
@@ -182,3 +190,50 @@ def test_the_stepwise_replay_stays_on_tiles():
     search = need - (coop.workspace_size(n, P, P) + 255) // 256 * 256
     at = search + _pick_at(coop, n, P, P)
     assert ws[at:at + 8].tolist() == [0xab] * 8
+
+
+# Batches by what they hold -> whether the search on subtiles takes them.
+LOOKS = {"short runs": 1, "few pinned": 0, "pinned at every pool's start": 0, "every other pool open": 0,
+         "pinned at both ends": 0, "one pool in 64 open": 0, "costs half zero": 1, "costs mostly zero": 0,
+         "mostly free": 0, "many requests, short runs": 1, "many requests, few pinned": 0,
+         "many requests, uneven costs": 1, "many requests, uneven costs, longer runs": 0,
+         "many requests, uneven costs, one long run": 0, "all pinned": 1}
+
+
+@pytest.mark.parametrize("what", LOOKS)
+def test_the_look_at_a_batch(what):
+    """The pick on batches of every kind, the kinds at an odd address too.
+    (Requests of 0 bytes: the look does not depend on them.)"""
+    import paper_2311_00591_amd as coop
+    print(f"[gpu case] look: {what}", flush=True)
+    many = what.startswith("many")
+    B, n = (16, 1 << 21) if many else (512, 65536)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    rand = lambda: torch.rand(B * n, generator=gen, device="cuda")
+    pos, pool = torch.arange(B * n, device="cuda") % n, torch.arange(B * n, device="cuda") // n
+    share = {"short runs": 0.3, "few pinned": 0.03, "every other pool open": 0.5, "one pool in 64 open": 0.3,
+             "pinned at both ends": 0, "costs half zero": 0.3, "costs mostly zero": 0.3, "mostly free": 0.3,
+             "many requests, short runs": 0.05, "many requests, uneven costs, longer runs": 0.002,
+             "all pinned": 1}.get(what, 0.01)
+    pinned = rand() < share
+    if what == "pinned at every pool's start": pinned |= pos < 8
+    if what == "every other pool open": pinned &= pool % 2 == 0
+    if what == "one pool in 64 open": pinned &= pool % 64 != 0
+    if what == "pinned at both ends": pinned = (pos < n // 12) | (pos >= n - n // 12)
+    if what.endswith("one long run"): pinned[B * n // 2:B * n // 2 + 400_000] = False
+    free = rand() < (0.8 if what == "mostly free" else 0.15)
+    cost = torch.exp(rand() * 27).long() if "uneven" in what else torch.randint(
+        1, 1000, (B * n,), generator=gen, device="cuda")
+    cost[rand() < {"costs half zero": 0.4, "costs mostly zero": 0.7}.get(what, 0)] = 0
+    kind = torch.where(pinned, 2, torch.where(free, 0, 1)).to(torch.uint8)
+    size = torch.full((B * n,), 512, dtype=torch.int64, device="cuda")
+    off = torch.arange(B + 1, device="cuda")
+    R = 64 if many else 1
+    req = torch.zeros(B * R, dtype=torch.int64, device="cuda")
+    for shift in (0, 5):
+        memory = torch.empty(B * n + shift, dtype=torch.uint8, device="cuda")
+        memory[shift:] = kind
+        ws = coop.WindowSearch(size, cost, memory[shift:], off * n, req, off * R)
+        assert (ws() == 0).all()
+        at = _pick_at(coop, B * n, B, B * R)
+        assert ws.workspace[at].item() == LOOKS[what], f"kinds shifted by {shift}"
