@@ -12,6 +12,7 @@ import test_gpu_replay as replay
 pytestmark = pytest.mark.gpu
 
 GRAIN = 512
+OUT_OF_SLOTS = -5  # the oracle's code for it
 
 
 def pools(blocks, ops, seed, ties, cap=None):
@@ -69,17 +70,50 @@ def test_edges_of_rounds_and_batches(blocks, ops, ties, policy):
 @pytest.mark.parametrize("policy", [replay.WINDOW, replay.GREEDY])
 @pytest.mark.parametrize("blocks,ops", [(1, 6), (2, 16), (64, 24), (257, 24), (1030, 24)])
 def test_pools_that_fill_their_slots(blocks, ops, policy):
-    """The fewest slots that the replay can do with: with no room at one end
-    the blocks at the other have to move, and with none at either end the pool
-    fills its slots."""
+    """The fewest slots that the replay can do with, so that some operation
+    leaves the pool with no slot to spare."""
     for seed in range(4):
         for cap in range(blocks, blocks + ops + 2):
             state, trace = pools(blocks, ops, seed, False, cap)
             try:
                 oracle.replay(state, trace, threads=8, policy=policy)
                 break
-            except Exception:  # the oracle refuses a replay that runs out of slots
+            except oracle.OracleError as e:  # it refuses a replay that runs out of slots
+                assert e.code == OUT_OF_SLOTS
                 continue
         label = f"full: {blocks} blocks in {cap} slots, {ops} operations, seed {seed}, {policy}"
         replay._announce(label)
         replay.assert_same(state, trace, label, policy)
+
+
+@pytest.mark.parametrize("policy", [replay.WINDOW, replay.GREEDY])
+@pytest.mark.parametrize("cap", [4, 5400])
+def test_an_eviction_that_leaves_no_slot(cap, policy):
+    """A full pool whose one evictable block is larger than the request: the
+    eviction stays done, the allocation fails for want of a slot for the rest,
+    and so does one that would fill the chunk exactly; once a neighbour is
+    released there is room.  Worked by hand (the oracle refuses a replay that
+    runs out of slots), in LDS and step by step."""
+    replay._announce(f"no slot left after an eviction: {cap} slots, policy {policy}")
+    MB, none = 1 << 20, (1 << 64) - 1
+    state = {"size": np.full(cap, MB, np.uint64), "cost": np.zeros(cap, np.uint64),
+             "kind": np.full(cap, 2, np.uint8), "id": np.arange(1, cap + 1, dtype=np.uint32),
+             "len": np.array([cap], np.uint64), "capacity": cap}
+    state["size"][1], state["cost"][1], state["kind"][1] = 8 * MB, 5, 1
+    a, b, c, d = cap + 1, cap + 2, cap + 3, cap + 4
+    trace = {"op": np.array([0, 0, 1, 0, 0], np.uint8), "op_id": np.array([a, b, 3, c, d], np.uint32),
+             "op_size": np.array([MB, 8 * MB, 0, 9 * MB, MB], np.uint64),
+             "op_cost": np.array([1, 1, 0, 6, 1], np.uint64), "op_flags": np.array([1, 1, 0, 1, 1], np.uint8)}
+    got_state, got, status = replay.gpu_replay(state, trace, policy)
+    assert status == 1
+    assert got["block"][0].tolist() == [none, none, 1, 1, 1]
+    evicted = [1, 2] if policy == replay.WINDOW else [1, none]
+    assert got["window"][0].tolist() == [evicted, [none] * 2, [none] * 2, [none] * 2, evicted]
+    assert got["cost"][0].tolist() == [5, 0, 0, 0, 6]
+    assert got["free"][0].tolist() == [0, none, none, none, 0]
+    # the last allocation's megabyte at the left end of the nine, the rest free
+    assert got_state["len"].tolist() == [cap]
+    assert got_state["size"].tolist() == [MB, MB, 8 * MB] + [MB] * (cap - 3)
+    assert got_state["kind"].tolist() == [2, 1, 0] + [2] * (cap - 3)
+    assert got_state["id"].tolist() == [1, d, 0] + list(range(4, cap + 1))
+    assert got_state["cost"].tolist() == [0, 1, 0] + [0] * (cap - 3)
