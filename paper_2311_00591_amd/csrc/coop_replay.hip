@@ -35,6 +35,8 @@
 
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "coop.h"
 #include "coop_host.h"
 
@@ -387,22 +389,13 @@ __global__ __launch_bounds__(kThreads) void replay_update_kernel(
 //              (ends never move left); then the lexicographic minimum of
 //              (cost, bytes, start) over the workgroup.
 // ---------------------------------------------------------------------------
-// 512 pools of 4096 operations took 6.65 ms (window policy) and 7.12 ms
+// 512 pools of 4096 operations took 6.68 ms (window policy) and 7.00 ms
 // (greedy) with 256 threads a pool, 7.54 and 7.45 with 128, 6.52 and 7.91 with
 // 512: fewer threads scan and move more slots each, more make the victim
 // search's partial results and the barriers dearer.
 constexpr uint32_t kResThreads = 256;
 constexpr uint32_t kResWaves = kResThreads / 64;
 constexpr size_t kStaticResLds = 1024;  // the capacity limit leaves this much for fixed LDS
-// Fixed LDS that the kernel uses, at most: two pools of 2632 slots then share
-// a CU (512 such pools of 1024 operations: 1.49 ms under the window policy and
-// 1.72 greedy; 2.61 and 2.96 with 784 bytes, one pool to a CU).
-constexpr size_t kFixedResLds = 304;
-// Wavefronts a SIMD, so pools a CU: five where the pools' LDS allows it (96
-// VGPRs and 4 spilled; 4096 pools of 192 operations: 1.17 ms under the window
-// policy and 1.37 greedy, 1.30 and 1.51 with four), else four without spills
-// (512 pools of 4096 operations: 6.74 and 7.08 ms, 6.76 and 7.10 with five).
-constexpr uint32_t kResSmall = 5, kResLarge = 4;
 
 // LDS bytes for a pool of cap slots, 31 a slot: size (which holds the byte
 // prefix sums during a window search), cost and cost prefix (u64), tensor id
@@ -697,9 +690,7 @@ __device__ WinKey res_window(const Lds& l, uint32_t n, uint64_t S, WinKey* wred,
 // Operations are read, and their outcomes written, this many at a time: the
 // records of the next batch are loaded while one is applied, so that no
 // operation waits for global memory (nor, the counter being shared, for the
-// stores of the operation before it).  What every wavefront reads of a record
-// lies in LDS; its cost, and the outcomes, stay in the registers of the lane
-// whose number they have.
+// stores of the operation before it).
 constexpr uint32_t kOpBatch = 8;
 
 struct OpRecord {
@@ -714,30 +705,63 @@ struct Outcome {
     uint64_t cost, free;
 };
 
+// The kernel's LDS beside the pool.  The lean form keeps the records' costs
+// and the outcomes in the registers of the lane (of the first wavefront) whose
+// number they have.
+struct LeanLds {
+    union {
+        WinKey wred[kResWaves];  // window policy
+        Victim vred[kResWaves];  // greedy policy
+        uint64_t red[kResWaves];
+    };
+    OpRecord rec[kOpBatch];
+    uint32_t hit[3];
+};
+
+struct FullLds : LeanLds {
+    uint64_t rec_cost[kOpBatch];
+    Outcome res[kOpBatch];
+};
+static_assert(kResThreads == 256, "a wavefront of a pool on every SIMD");
+static_assert(sizeof(LeanLds) <= 272 && sizeof(FullLds) <= kStaticResLds,
+              "lean: two pools of 2632 slots on a CU; the host leaves kStaticResLds beside the pool");
+
+constexpr size_t kLdsLimit = 160 * 1024;
+
+// Wavefronts a SIMD, so pools a CU, at most: 96 VGPRs.  4096 pools of 64 slots,
+// 192 operations: 1.17 ms (window policy) and 1.37 (greedy); 1.30 and 1.51
+// with four (99 VGPRs).
+constexpr uint32_t kResPools = 5;
+
+// The lean form for pools close below a share of a CU's LDS, of which the CU
+// then holds one more: 512 pools of 2632 slots, 1024 operations, 2.61 -> 1.49
+// ms (window policy), 2.96 -> 1.72 (greedy).  Its registers cost the others:
+// 512 pools of 2072 slots, 4096 operations, 6.68 ms, 6.76 lean (greedy 7.00,
+// 7.10).
+constexpr bool lean_pays(size_t pool_lds) {
+    const auto pools = [=](size_t fixed) {
+        const size_t n = kLdsLimit / (pool_lds + (fixed + 15) / 16 * 16);
+        return n < kResPools ? n : kResPools;
+    };
+    return pools(sizeof(LeanLds)) > pools(sizeof(FullLds));
+}
+
 // Bound by the chain of one pool's operations: each is a scan of the slots, a
 // barrier, and the replacement of a few slots with a move of those behind
 // them (a barrier between its reads and writes, one after).  A window or a
 // chunk is replaced by the tensor and what is left in one move.  512 pools of
-// 4096 operations: 8.72 -> 6.74 ms (window), 8.17 -> 7.08 ms (greedy) with
+// 4096 operations: 8.77 -> 6.68 ms (window), 8.17 -> 7.00 ms (greedy) with
 // records and outcomes in batches, one barrier a scan and one move an
 // allocation; before, every operation waited for its record's loads behind
 // the last one's stores.
-template <uint32_t Waves>
-__global__ __launch_bounds__(kResThreads, Waves) void replay_resident_kernel(
+template <bool Lean>
+__global__ __launch_bounds__(kResThreads, kResPools) void replay_resident_kernel(
     uint64_t* size, uint64_t* cost, uint8_t* kind, uint32_t* id, uint64_t* len, uint64_t cap,
     const uint8_t* op, const uint32_t* op_id, const uint64_t* op_size, const uint64_t* op_cost,
     const uint8_t* op_flags, uint64_t num_ops, int32_t policy, uint64_t* out_block,
     uint64_t* out_window, uint64_t* out_cost, uint64_t* out_free, uint32_t* status) {
     extern __shared__ __align__(16) char lds_raw[];
-    __shared__ union {
-        WinKey wred[kResWaves];  // window policy
-        Victim vred[kResWaves];  // greedy policy
-        uint64_t red[kResWaves];
-    } part;
-    __shared__ uint32_t hit[3];
-    __shared__ OpRecord rec[kOpBatch];
-    static_assert(sizeof(part) + sizeof(hit) + sizeof(rec) <= kFixedResLds && kFixedResLds <= kStaticResLds,
-                  "the host leaves this much LDS beside the pool");
+    __shared__ std::conditional_t<Lean, LeanLds, FullLds> sm;
     const uint32_t tid = threadIdx.x;
     const uint64_t b = blockIdx.x;
     const Lds l = lds_layout(lds_raw, cap);
@@ -746,10 +770,11 @@ __global__ __launch_bounds__(kResThreads, Waves) void replay_resident_kernel(
     uint32_t n = uniform(static_cast<uint32_t>(len0 < cap ? len0 : cap));
     for (uint32_t k = tid; k < n; k += kResThreads)
         res_put(l, k, Block{size[g + k], cost[g + k], id[g + k], kind[g + k]});
-    if (tid == 0) hit[0] = ~0u;
+    if (tid == 0) sm.hit[0] = ~0u;
     uint32_t turn = 0;
     OpRecord ahead{};
     uint64_t ahead_cost = 0, batch_cost = 0;
+    Outcome done{};
     const auto load = [&](uint64_t t) {
         const uint64_t o = o0 + t;
         ahead = OpRecord{op_size[o], op_id[o], op[o] | static_cast<uint32_t>(op_flags[o]) << 8};
@@ -764,22 +789,29 @@ __global__ __launch_bounds__(kResThreads, Waves) void replay_resident_kernel(
         out_cost[o] = r.cost;
         out_free[o] = r.free;
     };
-    Outcome done{};
+    // outcome tid of the batch at t0
+    const auto store_own = [&](uint64_t t0) {
+        if constexpr (Lean) store(t0 + tid, done);
+        else store(t0 + tid, sm.res[tid]);
+    };
     if (tid < kOpBatch && tid < num_ops) load(tid);
     for (uint64_t t0 = 0; t0 < num_ops; t0 += kOpBatch) {
-        if (tid < kOpBatch) rec[tid] = ahead;
-        batch_cost = ahead_cost;
-        if (tid < kOpBatch && t0 > 0) store(t0 - kOpBatch + tid, done);
-        if (tid < kOpBatch && t0 + kOpBatch + tid < num_ops) load(t0 + kOpBatch + tid);
+        if (tid < kOpBatch) {
+            sm.rec[tid] = ahead;
+            if constexpr (Lean) batch_cost = ahead_cost;
+            else sm.rec_cost[tid] = ahead_cost;
+            if (t0 > 0) store_own(t0 - kOpBatch);
+            if (t0 + kOpBatch + tid < num_ops) load(t0 + kOpBatch + tid);
+        }
         lds_barrier();
         const uint32_t count_ops =
             num_ops - t0 < kOpBatch ? static_cast<uint32_t>(num_ops - t0) : kOpBatch;
         for (uint32_t t = 0; t < count_ops; ++t) {
-            const OpRecord r = rec[t];
+            const OpRecord r = sm.rec[t];
             const uint32_t kop = uniform(r.op_flags & 0xffu), flags = r.op_flags >> 8;
             Outcome out{~0u, ~0u, ~0u, 0, kNone};
             if (kop == kOpFree) {
-                const uint32_t j = res_first(n, hit, turn, [&](uint32_t k) {
+                const uint32_t j = res_first(n, sm.hit, turn, [&](uint32_t k) {
                     return static_cast<int>(l.id[k] == r.id) & static_cast<int>(l.kd[k] != COOP_FREE);
                 });
                 if (j != ~0u) {
@@ -795,7 +827,7 @@ __global__ __launch_bounds__(kResThreads, Waves) void replay_resident_kernel(
                 }
             } else if (kop == kOpAlloc && r.size != 0 && r.id != 0) {
                 const uint64_t S = r.size;
-                uint32_t lo = res_first(n, hit, turn, [&](uint32_t k) {
+                uint32_t lo = res_first(n, sm.hit, turn, [&](uint32_t k) {
                     return static_cast<int>(l.sz[k] >= S) & static_cast<int>(l.kd[k] == COOP_FREE);
                 });
                 // the slots [lo, hi) that become the tensor and the rest of
@@ -809,12 +841,12 @@ __global__ __launch_bounds__(kResThreads, Waves) void replay_resident_kernel(
                     uint64_t fb = 0;
                     for (uint32_t j = tid; j < n; j += kResThreads)
                         if (l.kd[j] == COOP_FREE) fb += l.sz[j];
-                    const uint64_t free0 = res_sum(fb, part.red);
+                    const uint64_t free0 = res_sum(fb, sm.red);
                     uint32_t count = 0;
                     uint64_t evc = 0;
                     while (!evicted) {
                         const uint32_t v = uniform(
-                            greedy_victim(l.sz, l.co, l.kd, l.id, n, r.id, part.vred));
+                            greedy_victim(l.sz, l.co, l.kd, l.id, n, r.id, sm.vred));
                         if (v == ~0u) break;
                         ++count;
                         evc += l.co[v];
@@ -838,7 +870,7 @@ __global__ __launch_bounds__(kResThreads, Waves) void replay_resident_kernel(
                     ok = evicted;  // out of evictable tensors: fails, evictions stay
                 } else {
                     uint64_t fb;
-                    const WinKey wk = res_window(l, n, S, part.wred, &fb);
+                    const WinKey wk = res_window(l, n, S, sm.wred, &fb);
                     ok = evicted = wk.start != kNone;  // no window: fails, nothing changes
                     if (evicted) {
                         out.free = fb;
@@ -852,8 +884,11 @@ __global__ __launch_bounds__(kResThreads, Waves) void replay_resident_kernel(
                         hi = uniform(hi);
                     }
                 }
-                // (the first wavefront's lanes hold the costs, and it alone writes new blocks)
-                const Block tensor{S, readlane_u64(batch_cost, t), r.id,
+                // (lean: the first wavefront's lanes hold the costs, and it alone writes new blocks)
+                uint64_t r_cost;
+                if constexpr (Lean) r_cost = readlane_u64(batch_cost, t);
+                else r_cost = sm.rec_cost[t];
+                const Block tensor{S, r_cost, r.id,
                                    (flags & kFlagPinned) ? static_cast<uint8_t>(COOP_PINNED)
                                                            : static_cast<uint8_t>(COOP_EVICTABLE)};
                 if (ok && n - (hi - lo) + 2 > cap) {
@@ -877,13 +912,17 @@ __global__ __launch_bounds__(kResThreads, Waves) void replay_resident_kernel(
             } else if (kop == kOpAlloc) {
                 if (tid == 0) atomicOr(status, kErrOperation);
             }
-            if (tid == t) done = out;
+            if constexpr (Lean) {
+                if (tid == t) done = out;
+            } else if (tid == 0) {
+                sm.res[t] = out;
+            }
         }
         lds_barrier();
     }
     if (num_ops) {
         const uint64_t last = (num_ops - 1) / kOpBatch * kOpBatch;
-        if (tid < kOpBatch && last + tid < num_ops) store(last + tid, done);
+        if (tid < kOpBatch && last + tid < num_ops) store_own(last);
     }
     // the pool back to its slots; unused slots empty pinned blocks
     for (uint32_t k = tid; k < cap; k += kResThreads) {
@@ -895,8 +934,6 @@ __global__ __launch_bounds__(kResThreads, Waves) void replay_resident_kernel(
     }
     if (tid == 0) len[b] = n;
 }
-
-constexpr size_t kLdsLimit = 160 * 1024;
 
 struct ReplayLayout {
     size_t seg, req_off, req_ff, req_win, ff, win, status, ff_ws, win_ws, bytes;
@@ -960,8 +997,7 @@ coop_status_t coop_replay(uint64_t* size, uint64_t* cost, uint8_t* kind, uint32_
     if (capacity < 65536 && res_lds + kStaticResLds <= kLdsLimit) {
         hipLaunchKernelGGL(replay_status_kernel, dim3(1), dim3(1), 0, s0, status_out);
         if (hipGetLastError() != hipSuccess) return COOP_ERR_HIP;
-        const auto kernel = res_lds + kFixedResLds <= kLdsLimit / kResSmall
-                                ? replay_resident_kernel<kResSmall> : replay_resident_kernel<kResLarge>;
+        const auto kernel = lean_pays(res_lds) ? replay_resident_kernel<true> : replay_resident_kernel<false>;
         if (res_lds > 64 * 1024 &&
             hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                 hipFuncAttributeMaxDynamicSharedMemorySize,

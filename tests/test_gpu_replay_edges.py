@@ -68,6 +68,17 @@ def test_edges_of_rounds_and_batches(blocks, ops, ties, policy):
 
 
 @pytest.mark.parametrize("policy", [replay.WINDOW, replay.GREEDY])
+@pytest.mark.parametrize("cap", [1040, 1046, 2620, 2628, 2632, 2633, 2640])
+def test_pools_close_to_a_share_of_the_lds(cap, policy):
+    """Around a fifth and a half of a CU's LDS, the kernel has a form that
+    keeps costs and outcomes in registers."""
+    label = f"{cap} slots, policy {policy}"
+    replay._announce(label)
+    for ops in (7, 41):
+        replay.assert_same(*pools(900, ops, cap + ops, False, cap), f"{label}, {ops} operations", policy)
+
+
+@pytest.mark.parametrize("policy", [replay.WINDOW, replay.GREEDY])
 @pytest.mark.parametrize("blocks,ops", [(1, 6), (2, 16), (64, 24), (257, 24), (1030, 24)])
 def test_pools_that_fill_their_slots(blocks, ops, policy):
     """The fewest slots that the replay can do with, so that some operation
