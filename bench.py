@@ -36,9 +36,10 @@ FIT_METRIC = "first-fit queries/sec; % of HBM roofline"
 REPLAY_METRIC = "Algorithm 1 replay: allocator operations/sec over independent pools"
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E, published
 INFINITY_CACHE_BYTES = 256 << 20
-KERNEL = "coop_window_search_kernel"
 HEADLINE_CONFIG = 3   # the ragged heavy-tailed batch: the largest batch
-KERNEL_SOURCE = os.path.join(ROOT, "paper_2311_00591_amd", "csrc", "coop_window_search.hip")
+# the window search: two search kernels (a look at the batch picks one) and what they share
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2311_00591_amd", "csrc", name)
+                  for name in ("coop_window.h", "coop_window_search.hip", "coop_window_sub.hip")]
 
 
 def parse():
@@ -131,9 +132,20 @@ def copy_ceiling(dev, nbytes=1 << 30, reps=10):
 
 
 def source_digest(source=None):
-    """First 16 hex digits of the sha256 of a kernel's source file."""
-    with open(source or KERNEL_SOURCE, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    """First 16 hex digits of the sha256 of a kernel's source file (default:
+    of the window search's files, one after another)."""
+    h = hashlib.sha256()
+    for path in [source] if source else KERNEL_SOURCES:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
+
+
+def search_kernel(coop, pools, workspace):
+    """The kernel that searched the batch, as the workspace of its last call
+    says."""
+    at = coop._pick_offset(pools.num_blocks, pools.num_segments, pools.num_requests)
+    return "coop_window_sub_kernel" if at is not None and workspace[at].item() else "coop_window_search_kernel"
 
 
 def _profile_record(workload_name):
@@ -387,7 +399,7 @@ def bench_window_config(k, args, dev, cpu_budget, steps, warmup):
         roofline = dict(alu, per_request_hbm=hbm)
     else:
         roofline = dict(hbm, alu=alu)
-    roofline["kernel"] = KERNEL
+    roofline["kernel"] = search_kernel(coop, pools, workspace)
     roofline["valu_issue"] = valu_issue(spec.name, block_queries, t)
     single = None
     if args.medians:

@@ -109,6 +109,18 @@ def plan_info(num_blocks: int, num_segments: int, num_requests: int) -> dict:
     return {name: int(getattr(plan, name)) for name, _ in CoopPlan._fields_}
 
 
+def _pick_offset(num_blocks: int, num_segments: int, num_requests: int) -> Optional[int]:
+    """Where the workspace of a search of these counts holds the word that says
+    which search kernel took the batch (1: the one on subtiles, 0: the one on
+    tiles); None for batches that only the one on tiles takes.  For the
+    benchmark and the tests."""
+    plan = plan_info(num_blocks, num_segments, num_requests)
+    if plan["units"] < 16 * plan["workgroups"] or num_blocks // 8192 < num_segments:
+        return None
+    shared = num_requests if num_requests <= 1 << 17 and plan["partial_slots"] > 1 else 0
+    return workspace_size(num_blocks, num_segments, num_requests) - 8 * shared - 8
+
+
 def _u64_tensor(t: torch.Tensor, name: str, device) -> torch.Tensor:
     if t.dtype not in (torch.int64, torch.uint64):
         raise TypeError(f"{name} must be int64/uint64 storage, got {t.dtype}")

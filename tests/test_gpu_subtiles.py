@@ -19,13 +19,6 @@ EDGES = [1, 7, 8, 9, 511, 512, 513, 575, 576, 577, 1599, 1600, 1601, 4095, 4096,
          8191, 8192, 8193]
 
 
-def _pick_at(coop, n, B, Q):
-    """Where a search's workspace holds the word that says which kernel took
-    the batch (1: subtiles): its last word but for the shared bounds."""
-    shared = Q <= 1 << 17 and coop.plan_info(n, B, Q)["partial_slots"] > 1
-    return coop.workspace_size(n, B, Q) - 8 * (Q if shared else 0) - 8
-
-
 def _batch(pinned, cost, seed, every=4):
     """Snapshots at the edges, and one long one per edge that brings the
     average to more than 8192 blocks; one long one in `every` has no pinned
@@ -79,7 +72,7 @@ def test_large_batches(pinned, cost, every, subtiles):
     memory = torch.zeros(nbytes, dtype=torch.uint8, device="cuda")
     memory[nbytes * 9 // 10:] = 255
     ws = coop.WindowSearch(*coop.to_device(a, "cuda"), workspace=memory)
-    at = _pick_at(coop, a.num_blocks, a.num_segments, a.num_requests)
+    at = coop._pick_offset(a.num_blocks, a.num_segments, a.num_requests)
 
     def check(label):
         torch.cuda.synchronize()
@@ -154,7 +147,7 @@ def test_shortest_snapshots_with_windows_past_the_walk():
         torch.cuda.synchronize()
         got = ws.out.cpu().numpy().view(np.uint64)
         bad = np.flatnonzero((got != want).any(axis=1))
-        at = _pick_at(coop, a.num_blocks, a.num_segments, a.num_requests)
+        at = coop._pick_offset(a.num_blocks, a.num_segments, a.num_requests)
         assert memory[at].item() == 1
         assert len(bad) == 0, f"memory of {fill}: {len(bad)} differ, first {int(bad[0])}: {got[bad[0]]}, {want[bad[0]]}"
 
@@ -188,7 +181,7 @@ def test_the_stepwise_replay_stays_on_tiles():
     assert (rep.block.view(P, 3) == torch.tensor([1, -1, 1], device="cuda")).all()
     assert (rep.window.view(P, 3, 2)[:, 2] == torch.tensor([1, 3], device="cuda")).all()
     search = need - (coop.workspace_size(n, P, P) + 255) // 256 * 256
-    at = search + _pick_at(coop, n, P, P)
+    at = search + coop._pick_offset(n, P, P)
     assert ws[at:at + 8].tolist() == [0xab] * 8
 
 
@@ -235,5 +228,5 @@ def test_the_look_at_a_batch(what):
         memory[shift:] = kind
         ws = coop.WindowSearch(size, cost, memory[shift:], off * n, req, off * R)
         assert (ws() == 0).all()
-        at = _pick_at(coop, B * n, B, B * R)
+        at = coop._pick_offset(B * n, B, B * R)
         assert ws.workspace[at].item() == LOOKS[what], f"kinds shifted by {shift}"
