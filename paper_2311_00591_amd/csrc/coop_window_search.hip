@@ -56,7 +56,9 @@
 // array, stages no halo, and bisects per start.
 //
 // Large batches of short runs, or with many requests on a snapshot, are
-// searched by coop_window_sub_kernel instead (coop_window.h has the rule):
+// searched by coop_window_sub_kernel instead (coop_window.h has the rule on
+// sizes, coop_window_sub.hip the one on contents, which costs the batches it
+// refuses 7 to 10 us: 662 -> 671 us, 237 -> 247 for the smallest):
 // eighths of a tile by single wavefronts, which look only at starts that can
 // still win.  It fills the same partial slots, tickets, records and deferred
 // list.

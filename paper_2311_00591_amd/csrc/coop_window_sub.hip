@@ -1,15 +1,19 @@
 // The window search on subtiles: the search kernel of large batches whose
-// windows are short or whose costs are uneven (coop_window.h says which;
-// planning, the second kernel and the C entry points are in
-// coop_window_search.hip).
+// windows are short or whose costs are uneven (coop_window.h says which sizes,
+// subtiles_pay below which contents; planning, the second kernel and the C
+// entry points are in coop_window_search.hip).
 //
 // A merge of all starts with all ends reads two records of LDS per start and
 // request, whether or not the window can win: it was bound by LDS reads and
 // the instructions around them.  Here a request looks at a start only if the
 // start's first blocks do not already cost more than the best window known,
 // which a comparison of one-byte codes tells, four starts to an instruction.
-// Mixed batch of 66e6 blocks and 16384 requests: 705 -> 487 us; one pool of
-// 2^24 blocks and 4096 requests: 98.4 -> 67.0 ms.
+// Mixed batch of 66e6 blocks and 16384 requests: 709 -> 497 us; one pool of
+// 2^24 blocks and 4096 requests: 98.3 -> 68.3 ms.  What is left (counted): of a
+// request and a subtile's 512 starts, 4.8 are probed and 1.1 searched for in
+// the mixed batch, so staging the subtiles leads there; in the huge pool 35 and
+// 26 are, and these searches take the time (windows that leave the subtile are
+// walked for in 0.6% of the pairs).
 
 #include "coop_window.h"
 
@@ -51,8 +55,9 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
 // Keys, tickets, partial results
 // ---------------------------------------------------------------------------
 
-// The walk over the units and the snapshot list.  Only wavefront 0 of a
-// workgroup moves it, once a tile, and its state waits in LDS in between: held
+// The walk over the units and the snapshot list.  One wavefront of a workgroup
+// at a time moves it, the first to end a job's last pass (a barrier follows
+// before the next can), and its state waits in LDS in between: held
 // in scalar registers by every wavefront, with the next job and the launch
 // parameters, it had most of them spilled to vector lanes (a fifth of the
 // search kernel's vector instructions moved such values).
@@ -1223,8 +1228,7 @@ __device__ __forceinline__ void add_record(const Params& P, RecSum& rec, uint32_
 }
 
 // The search of every unit the workgroup gets: its first chunk, then chunks
-// from the queue.  raw is a block's cost; store(q, key, S) writes
-// request q's result.
+// from the queue.
 __device__ __forceinline__ void search_units(const Params& P, SearchSmem& sm) {
     const uint32_t tid = threadIdx.x;
     const uint32_t w = uniform(tid >> 6);
