@@ -177,7 +177,6 @@ struct Params {
     uint64_t epoch;        // this call's tag on the arrival tickets
     const uint64_t* tag_word;  // captured calls: the workspace word the tags come from
     uint32_t defer_cap;    // deferred entries, at most (the arrays: see Ext)
-    uint32_t subtiles;     // it did (set by the second kernel)
     uint32_t slices_log2;  // request slices (a power of two): slice y takes y, y + slices, ...
     double inv_slope;      // guess of b per tile id, for the first snapshot lookup
 };
