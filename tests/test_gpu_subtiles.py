@@ -230,3 +230,27 @@ def test_the_look_at_a_batch(what):
         assert (ws() == 0).all()
         at = coop._pick_offset(B * n, B, B * R)
         assert ws.workspace[at].item() == LOOKS[what], f"kinds shifted by {shift}"
+
+
+def test_many_requests_on_one_pool():
+    """Requests in passes of 64 over every tile, slices of them, bounds shared
+    by all workgroups, and costs so uneven that the look takes the pool with
+    few pinned blocks; one run longer than the walk."""
+    import paper_2311_00591_amd as coop
+    rng = np.random.default_rng(3)
+    n, R = 1 << 22, 4096
+    print(f"[gpu case] subtiles: one pool of {n} blocks, {R} requests", flush=True)
+    size = (rng.integers(1, 1 << 12, n) * 512).astype(np.uint64)
+    u = rng.random(n)
+    kind = np.where(u < 0.01, 2, np.where(u < 0.2, 0, 1)).astype(np.uint8)
+    kind[3_000_000:3_009_500] = np.minimum(kind[3_000_000:3_009_500], 1)
+    cost = np.where(kind == 1, np.exp(rng.random(n) * np.log(1e12)), 0).astype(np.uint64)
+    req = (np.exp(rng.random(R) * np.log(9400)) * (1 << 20)).astype(np.uint64)
+    a = workloads.Pools(size, cost, kind, np.array([0, n], np.uint64), req, np.array([0, R], np.uint64))
+    ws = coop.WindowSearch(*coop.to_device(a, "cuda"))
+    got = ws().cpu().numpy().view(np.uint64)
+    assert ws.workspace[coop._pick_offset(n, 1, R)].item() == 1
+    want = oracle.window_search(*a.arrays(), threads=min(16, len(os.sched_getaffinity(0))))
+    assert (want[:, 1] - want[:, 0])[want[:, 0] != (1 << 64) - 1].max() > 8192
+    bad = np.flatnonzero((got != want).any(axis=1))
+    assert len(bad) == 0, f"{len(bad)} differ, first {int(bad[0])}"
